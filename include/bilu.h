@@ -280,8 +280,9 @@ bilu_status bilu_apply_point(bilu_ctx* ctx, const double* r, double* z, hipStrea
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same kernels and the same result bits as bilu_apply, with the
  * intermediate vector and the sweeps' counters in a fixed 32 MiB scratch
- * array of the library (one per device, held until the process ends); calls
- * no hipMalloc, hipFree or allocating routine.  nb*bs*nrhs doubles must fit
+ * array of the library (one per device, held until the process ends), or,
+ * where mode 2 sweeps blocks of grid lines, in the context's own work space;
+ * calls no hipMalloc, hipFree or allocating routine.  nb*bs*nrhs doubles must fit
  * in 32 MiB - 256 bytes, else BILU_ERR_ARG.  The layouts must already hold
  * the current factors (they do after bilu_factor_diag for nrhs = 1, or after
  * one bilu_apply with the same nrhs), else BILU_ERR_STATE, as when the
@@ -327,7 +328,10 @@ enum {
     BILU_TUNE_SWEEP_MODE = 0, /* 0: one launch per level; 1: one persistent launch per
                                  sweep over level chunks; 2: one persistent launch per
                                  sweep over row tiles, one wavefront per (tile,
-                                 right-hand side) (default)                          */
+                                 right-hand side) (default).  On a pattern in
+                                 natural grid order mode 2 sweeps blocks of grid
+                                 lines instead while every knob below that shapes
+                                 the row tiles or their launches has its default   */
     BILU_TUNE_TILE_ROWS = 1,  /* block rows per tile in mode 2 (capped so a tile's
                                  values fit 64 KiB of LDS); 0 = chosen by a host
                                  simulation of the tiled schedule (default)          */

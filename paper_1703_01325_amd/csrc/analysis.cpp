@@ -128,13 +128,6 @@ int sweep_levels(int nb, const std::vector<int32_t>& Pp, const std::vector<int32
     return nlev;
 }
 
-namespace {
-
-struct Dep {
-    int32_t col;
-    int64_t src;
-};
-
 // Dependencies of every row of a sweep, in ascending column order.
 void sweep_deps(const Host& h, int which, std::vector<int32_t>& ptr, std::vector<Dep>& deps)
 {
@@ -167,8 +160,6 @@ void sweep_deps(const Host& h, int which, std::vector<int32_t>& ptr, std::vector
                 if (ut ? upper(i, e) : lower(i, e)) deps[fill[h.Pj[e]]++] = Dep{i, e};
     }
 }
-
-}  // namespace
 
 // Level sets plus the chunked layout of one sweep.  Inside a level the rows
 // are independent, so the chunks may order them freely: rows are sorted by
@@ -476,12 +467,9 @@ void build_tiled(const Host& h, int which, int rpc, int tile_rows, int group, in
 bool grid_lines(const Host& h, int& nx, int& nxy)
 {
     const int nb = h.nb;
-    std::vector<int32_t> dptr;
-    std::vector<Dep> deps;
-    sweep_deps(h, BILU_SWEEP_L, dptr, deps);
     auto has = [&](int32_t i, int32_t d) {
-        for (int32_t e = dptr[i]; e < dptr[i + 1]; ++e)
-            if (deps[e].col == i - d) return true;
+        for (int32_t e = h.Pp[i]; e < h.Pp[i + 1] && h.Pj[e] < i; ++e)
+            if (h.Pj[e] == i - d) return true;
         return false;
     };
     // line starts: rows without a dependency on the previous row

@@ -17,6 +17,7 @@
 #include "kernels.h"
 #include "kernels_batch.h"
 #include "launch.h"
+#include "pencil_kernels.h"
 
 using namespace bilu;
 using dev::KState;
@@ -137,6 +138,12 @@ struct bilu_ctx {
     bool form_uploaded[kForms] = {false, false, false};
     int line_block = 0;         // line sweep of L and U' with blocks ny + 256*nz (0: off)
     bool layouts_checked = false;   // validate_layout passed on the layouts as built
+    // pencil sweeps (use_pencil): layouts, the vector between the two sweeps
+    // of an application, and off where a caller reads the row-tile layouts
+    DevPencil pencil[4];
+    double* d_pw = nullptr;
+    size_t pw_cap = 0;
+    bool pencil_off = false;
 
     double* d_y = nullptr;      // intermediate of an application, kept at kNotReady
     size_t y_cap = 0;
@@ -328,6 +335,26 @@ bool launch_pairs(int bs, int kmax, int prec, bool fuse, int blocks, size_t lds,
 bool launch_helped(int bs, int kmax, int prec, bool fuse, int blocks, size_t lds, hipStream_t s, const TiledArgs& a)
 {
     BILU_SWITCH_B(bs, if (!launch::helped<B>(kmax, prec, fuse, blocks, lds, s, a)) return false)
+}
+
+bool launch_pencil(int bs, int width, int cb, int prec, bool fuse, int blocks, size_t lds, hipStream_t s,
+                   const dev::PencilArgs& a)
+{
+    BILU_SWITCH_B(bs, if (!launch::pencil<B>(width, cb, prec, fuse, blocks, lds, s, a)) return false)
+}
+
+// Factor values of a pencil layout (k_layout_pencil).
+template <typename T>
+bool layout_pencil_t(int bs, const HostPencil& hp, const bilu_ctx* c, int up, int tr, hipStream_t s)
+{
+    const DevPencil& d = c->pencil[hp.which];
+    const int kb = hp.width * bs, v = 16 / static_cast<int>(sizeof(T));
+    const int64_t units =
+        static_cast<int64_t>(hp.nchunks) * (kb / v + (kb % v >= 2) + kb % 2 + pencil_meta_quads(hp.width));
+    BILU_SWITCH_B(bs, hipLaunchKernelGGL((dev::k_layout_pencil<B, T>), dim3(grid_for(units, 4)), dim3(256), 0, s,
+                                         static_cast<int64_t>(hp.nchunks), hp.width, d.src,
+                                         reinterpret_cast<const int4*>(d.meta), c->d_Prow, c->d_P, c->d_Dinv, up, tr,
+                                         d.recs))
 }
 
 bool launch_lines(int bs, int prec, bool fuse, int blocks, hipStream_t s, const dev::LineArgs& a)
@@ -732,6 +759,28 @@ bilu_status ensure_device(bilu_ctx* c)
 // 31-bit byte offsets, so the (n x R) vectors must stay below 2 GiB), level
 // chunks otherwise.
 // Sweep `which` of R columns runs as a line sweep.
+int persistent_blocks(bilu_ctx* c, int units, int units_per_block, int per_cu)
+{
+    const int want = std::max(1, (units + units_per_block - 1) / units_per_block);
+    const int cap = c->blocks_override > 0 ? c->blocks_override : c->num_cu * per_cu;
+    return std::max(1, std::min(want, cap));
+}
+
+int64_t pencil_lds(const bilu_ctx* c, const HostPencil& hp, int cb)
+{
+    return pencil_lds_bytes(hp.ring, hp.ext_ring, hp.rpc, c->h.bs, cb);
+}
+
+// Right-hand-side columns a pencil workgroup sweeps together: two where the
+// tickets of single columns would fill the chip three times over (two
+// workgroups per compute unit), so that loading each factor value once for two
+// columns pays; below that a pair's longer step only lengthens the chain.
+int pencil_columns(const bilu_ctx* c, const HostPencil& hp, int ncol)
+{
+    const bool full = static_cast<int64_t>(hp.ntiles) * ncol >= int64_t(6) * c->num_cu;
+    return ncol % 2 == 0 && full && hp.width <= kPencilPairWidth && pencil_lds(c, hp, 2) <= c->lds_max ? 2 : 1;
+}
+
 bool use_lines(const bilu_ctx* c, int which, int R)
 {
     return c->line_block > 0 && R == 1 && c->sweep_mode == 2 && c->h.lines[which].built;
@@ -807,6 +856,179 @@ bilu_status layout_form(bilu_ctx* c, int form, hipStream_t s)
     return BILU_OK;
 }
 
+// An application runs as a pair of pencil sweeps where no layout was asked
+// for (every knob of the row tiles at its automatic value) and the pattern has
+// a pencil layout for both: grid lines in natural order and rows no wider than
+// the kernels.  Every pattern measured that has one ran faster that way (2 to
+// 7 times, figures at k_sweep_pencil), so there is no other condition.
+bool pencil_wanted(const bilu_ctx* c)
+{
+    return !c->pencil_off && !c->values_only && c->sweep_mode == 2 && c->h.bs <= kMaxKernelBs &&
+           c->tile_rows_req == 0 && c->tile_group_req == 0 && c->tile_block == 0 && c->line_block == 0 &&
+           c->helper == 0 && c->rhs_pairs == 0 && c->split_dinv == 0 && !c->fuse_spmv && c->blocks_override == 0;
+}
+
+bool use_pencil(bilu_ctx* c, bool transpose, int R)
+{
+    if (!pencil_wanted(c) || sweep_form(c, R) != kFormTiled) return false;
+    for (int w : {transpose ? BILU_SWEEP_UT : BILU_SWEEP_L, transpose ? BILU_SWEEP_LT : BILU_SWEEP_U}) {
+        if (!c->h.sweep[w].built) return false;
+        HostPencil& hp = c->h.pencil[w];
+        if (!hp.tried) build_pencil(c->h, w, c->h.rpc, hp);
+        if (!hp.built || pencil_lds(c, hp, 1) > c->lds_max) return false;
+    }
+    return true;
+}
+
+// Pencil layouts of both sweeps on the device, with the current factors.
+bilu_status layout_pencil(bilu_ctx* c, bool transpose, hipStream_t s)
+{
+    bilu_status st;
+    for (int w : {transpose ? BILU_SWEEP_UT : BILU_SWEEP_L, transpose ? BILU_SWEEP_LT : BILU_SWEEP_U}) {
+        const HostPencil& hp = c->h.pencil[w];
+        DevPencil& d = c->pencil[w];
+        if (!d.tile_ptr) {
+            // no kernel ever runs on a layout that fails the host self-check
+            if (validate_pencil(c->h, hp) != BILU_OK) return BILU_ERR_STATE;
+            // rows and exchange entries by their first element
+            const int bs = c->h.bs;
+            std::vector<int32_t> rows(2 * (hp.rows.size() + static_cast<size_t>(kPencilSlack) * hp.rpc), -1);
+            for (size_t i = 0; i < hp.rows.size(); ++i) {
+                if (hp.rows[i] >= 0) rows[2 * i] = hp.rows[i] * bs;
+                if (hp.entry[i] >= 0) rows[2 * i + 1] = hp.entry[i] * bs;
+            }
+            std::vector<int32_t> ext(4 * hp.ext_idx.size());
+            for (int t = 0; t < hp.ntiles; ++t)
+                for (int e = hp.ext_ptr[t]; e < hp.ext_ptr[t + 1]; ++e) {
+                    const size_t i = 4 * static_cast<size_t>(e);
+                    ext[i] = hp.ext_idx[e] * bs;
+                    ext[i + 1] = kPencilZeroBytes + hp.ring * kPencilSlotBytes +
+                                 (e - hp.ext_ptr[t]) % hp.ext_ring * bs * 8;
+                    ext[i + 2] = hp.ext_free[e];
+                }
+            if ((st = upload(c, &d.ext_ptr, hp.ext_ptr)) || (st = upload(c, &d.rows, rows)) ||
+                (st = upload(c, &d.meta, hp.meta)) || (st = upload(c, &d.src, hp.src)) ||
+                (st = upload(c, &d.ext, ext)) || (st = upload(c, &d.tile_ptr, hp.tile_ptr)))
+                return st;
+        }
+        if (d.vals_precision == c->precision) continue;
+        const bool f32 = c->precision == BILU_FACTORS_FP32;
+        const size_t rec = static_cast<size_t>(hp.width) * c->h.bs * 64 * (f32 ? 4 : 8) +
+                           static_cast<size_t>(pencil_meta_quads(hp.width)) * hp.rpc * 16;
+        const size_t bytes = rec * (static_cast<size_t>(hp.nchunks) + kPencilSlack);
+        if (!d.recs || d.recs_bytes != bytes) {
+            dfree(c, d.recs);
+            d.recs = nullptr;
+            d.recs_bytes = 0;
+            if ((st = dalloc(c, &d.recs, bytes))) return st;
+            d.recs_bytes = bytes;
+            const int64_t slack = static_cast<int64_t>(rec * kPencilSlack / 4);
+            hipLaunchKernelGGL(dev::k_fill_i32, dim3(grid_for(slack)), dim3(256), 0, s, slack,
+                               reinterpret_cast<int32_t*>(d.recs + rec * hp.nchunks), 0);
+        }
+        const int tr = transposed_sweep(w) ? 1 : 0;
+        const int up = (w == BILU_SWEEP_U || w == BILU_SWEEP_UT) ? 1 : 0;
+        const bool ok = f32 ? layout_pencil_t<float>(c->h.bs, hp, c, up, tr, s)
+                            : layout_pencil_t<double>(c->h.bs, hp, c, up, tr, s);
+        if (!ok) return BILU_ERR_ARG;
+        CK(hipGetLastError());
+        d.vals_precision = c->precision;
+    }
+    return BILU_OK;
+}
+
+// Work space of an application by pencil sweeps of R columns.
+bool pencil_work_fits(const bilu_ctx* c, bool transpose, int R)
+{
+    if (c->pw_cap < static_cast<size_t>(c->h.nb) * c->h.bs * R) return false;
+    for (int w : {transpose ? BILU_SWEEP_UT : BILU_SWEEP_L, transpose ? BILU_SWEEP_LT : BILU_SWEEP_U})
+        if (c->pencil[w].exch_cap < static_cast<size_t>(c->h.pencil[w].nexch) * c->h.bs * R) return false;
+    return true;
+}
+
+bilu_status ensure_pencil_work(bilu_ctx* c, bool transpose, int R, hipStream_t s)
+{
+    bilu_status st;
+    const size_t need = static_cast<size_t>(c->h.nb) * c->h.bs * R;
+    if (c->pw_cap < need) {
+        dfree(c, c->d_pw);
+        c->d_pw = nullptr;
+        c->pw_cap = 0;
+        if ((st = dalloc(c, &c->d_pw, need))) return st;
+        c->pw_cap = need;
+    }
+    for (int w : {transpose ? BILU_SWEEP_UT : BILU_SWEEP_L, transpose ? BILU_SWEEP_LT : BILU_SWEEP_U}) {
+        DevPencil& d = c->pencil[w];
+        const size_t ne = static_cast<size_t>(c->h.pencil[w].nexch) * c->h.bs * R;
+        if (d.exch_cap >= ne && d.exch) continue;
+        dfree(c, d.exch);
+        d.exch = nullptr;
+        d.exch_cap = 0;
+        if ((st = dalloc(c, &d.exch, std::max<size_t>(ne, 1)))) return st;
+        d.exch_cap = ne;
+        hipLaunchKernelGGL(dev::k_fill_not_ready, dim3(grid_for(static_cast<int64_t>(ne))), dim3(256), 0, s,
+                           static_cast<int64_t>(ne), d.exch);
+        CK(hipGetLastError());
+    }
+    return BILU_OK;
+}
+
+// One pencil sweep of ncol columns of rhs (rows of rhs_R columns) into out
+// (rows of out_R columns); fuse: the second sweep of the pair, whose right-hand
+// side is D^{-1} (its transpose for the transposed pair) times rhs.
+bilu_status run_pencil(bilu_ctx* c, int which, int other, const double* rhs, int rhs_R, double* out, int out_R,
+                       int ncol, bool fuse, hipStream_t s, const int* gate, bool timed)
+{
+    const long tslot = timed ? timing_begin(c, BILU_K_SWEEP_L + which, s) : -1;
+    const HostPencil& hp = c->h.pencil[which];
+    const DevPencil& d = c->pencil[which];
+    const int cb = pencil_columns(c, hp, ncol);
+    dev::PencilArgs a{};
+    a.tile_ptr = d.tile_ptr;
+    a.ext_ptr = d.ext_ptr;
+    a.rows = reinterpret_cast<const int2*>(d.rows);
+    a.recs = d.recs;
+    a.ext = reinterpret_cast<const int4*>(d.ext);
+    a.dinv = c->d_Dinv;
+    a.rhs = rhs;
+    a.out = out;
+    a.exch = d.exch;
+    a.reset = c->pencil[other].exch;
+    a.nreset = c->h.pencil[other].nexch * c->h.bs * ncol;
+    a.nexch = hp.nexch;
+    a.ticket = c->d_ticket;
+    a.done = c->d_done;
+    a.status = c->d_status;
+    a.gate = gate;
+    a.ntiles = hp.ntiles;
+    a.ncg = ncol / cb;
+    a.ring = hp.ring;
+    a.reach = hp.reach;
+    a.ext_ring = hp.ext_ring;
+    a.rhs_R = rhs_R;
+    a.out_R = out_R;
+    a.transposed = transposed_sweep(which) ? 1 : 0;
+    a.spin_limit = c->spin_limit;
+    const int blocks = persistent_blocks(c, hp.ntiles * a.ncg, 1, 2);
+    a.total_waves = static_cast<unsigned int>(blocks);
+    if (!launch_pencil(c->h.bs, hp.width, cb, c->precision, fuse, blocks, static_cast<size_t>(pencil_lds(c, hp, cb)), s, a))
+        return BILU_ERR_ARG;
+    timing_end(c, tslot, s);
+    CK(hipGetLastError());
+    return BILU_OK;
+}
+
+// z = M^{-1} r (or M^{-T} r): columns [0, ncol) of r and z, rows of R columns.
+bilu_status pencil_pair(bilu_ctx* c, const double* r, double* z, int R, int ncol, bool transpose, hipStream_t s,
+                        const int* gate, bool timed = true)
+{
+    const int first = transpose ? BILU_SWEEP_UT : BILU_SWEEP_L;
+    const int second = transpose ? BILU_SWEEP_LT : BILU_SWEEP_U;
+    bilu_status st = run_pencil(c, first, second, r, R, c->d_pw, ncol, ncol, false, s, gate, timed);
+    if (st) return st;
+    return run_pencil(c, second, first, c->d_pw, ncol, z, R, ncol, true, s, gate, timed);
+}
+
 // D^{-1} y by blocks ahead of an unfused U' sweep instead of inside it
 // (BILU_TUNE_SPLIT_DINV): one right-hand side, tiled U' layout;
 // automatically where U' rows keep six or more dependency slots in
@@ -851,12 +1073,6 @@ bilu_status ensure_y(bilu_ctx* c, int R, hipStream_t s)
     return BILU_OK;
 }
 
-int persistent_blocks(bilu_ctx* c, int units, int units_per_block, int per_cu)
-{
-    const int want = std::max(1, (units + units_per_block - 1) / units_per_block);
-    const int cap = c->blocks_override > 0 ? c->blocks_override : c->num_cu * per_cu;
-    return std::max(1, std::min(want, cap));
-}
 
 #ifdef BILU_TRACE
 long long* g_trace_buf[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -1196,6 +1412,10 @@ bilu_status do_apply(bilu_ctx* c, const double* r, double* z, int R, bool transp
     const int second = transpose ? BILU_SWEEP_LT : BILU_SWEEP_U;
     if (!c->h.sweep[first].built || !c->h.sweep[second].built) return BILU_ERR_STATE;
     bilu_status st;
+    if (use_pencil(c, transpose, R)) {
+        if ((st = layout_pencil(c, transpose, s)) || (st = ensure_pencil_work(c, transpose, R, s))) return st;
+        return pencil_pair(c, r, z, R, R, transpose, s, gate);
+    }
     const int form = sweep_form(c, R);
     if ((st = layout_form(c, form, s))) return st;
     if ((use_lines(c, first, R) || use_lines(c, second, R)) && (st = layout_form(c, kFormLines, s))) return st;
@@ -1402,6 +1622,15 @@ bilu_status bilu_get_info(const bilu_ctx* c, bilu_info* info)
 bilu_status bilu_validate(const bilu_ctx* c)
 {
     if (!c) return BILU_ERR_ARG;
+    // the pencil layouts too, also before the first factorisation builds them
+    if (pencil_wanted(c))
+        for (int w = 0; w < 4; ++w) {
+            if (!c->h.sweep[w].built) continue;
+            HostPencil hp;
+            if (!c->h.pencil[w].tried) build_pencil(c->h, w, c->h.rpc, hp);
+            const HostPencil& use = c->h.pencil[w].tried ? c->h.pencil[w] : hp;
+            if (use.built && validate_pencil(c->h, use) != BILU_OK) return BILU_ERR_STATE;
+        }
     return static_cast<bilu_status>(validate_layout(c->h));
 }
 
@@ -1475,8 +1704,17 @@ bilu_status bilu_factor_diag(bilu_ctx* c, int precision, hipStream_t s)
     c->precision = precision;
     for (int f = 0; f < kForms; ++f)
         for (int w = 0; w < 4; ++w) c->ds[f][w].vals_precision = -1;
-    bilu_status st = layout_form(c, sweep_form(c, 1), s);
-    if (st) return st;
+    for (DevPencil& d : c->pencil) d.vals_precision = -1;
+    bilu_status st;
+    if (use_pencil(c, false, 1)) {
+        // the transposed pair's layouts too, as the row tiles' are
+        for (bool tr : {false, true})
+            if (use_pencil(c, tr, 1) &&
+                ((st = layout_pencil(c, tr, s)) || (st = ensure_pencil_work(c, tr, 1, s))))
+                return st;
+    } else if ((st = layout_form(c, sweep_form(c, 1), s))) {
+        return st;
+    }
     if (use_lines(c, BILU_SWEEP_L, 1) || use_lines(c, BILU_SWEEP_U, 1)) {
         if ((st = layout_form(c, kFormLines, s))) return st;
     }
@@ -1543,6 +1781,22 @@ bilu_status bilu_apply_noalloc(bilu_ctx* c, const double* r, double* z, int nrhs
     const int64_t ny = static_cast<int64_t>(c->h.nb) * c->h.bs * nrhs;
     if (static_cast<size_t>(ny) * sizeof(double) > kScratchBytes - kScratchHeader) return BILU_ERR_ARG;
     if (!c->dev_ready || !c->split_done) return BILU_ERR_STATE;
+    if (use_pencil(c, false, nrhs)) {
+        // work space of the context: columns it does not hold together run
+        // one after the other (the factorisation made room for one)
+        int device = -1;
+        CK(hipGetDevice(&device));
+        if (device != c->device) return BILU_ERR_STATE;
+        for (int w : {static_cast<int>(BILU_SWEEP_L), static_cast<int>(BILU_SWEEP_U)})
+            if (c->pencil[w].vals_precision != c->precision) return BILU_ERR_STATE;
+        const int ncol = pencil_work_fits(c, false, nrhs) ? nrhs : 1;
+        if (!pencil_work_fits(c, false, ncol)) return BILU_ERR_STATE;
+        for (int j = 0; j < nrhs; j += ncol) {
+            const bilu_status st = pencil_pair(c, r + j, z + j, nrhs, ncol, false, s, nullptr, false);
+            if (st) return st;
+        }
+        return BILU_OK;
+    }
     // the layouts of this form must already hold the current factors: laying
     // them out would allocate
     const int form = sweep_form(c, nrhs);

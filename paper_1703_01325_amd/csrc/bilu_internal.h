@@ -155,6 +155,93 @@ inline int32_t tiled_local_code(int32_t local_row, int bs)
     return static_cast<int32_t>(0x80000000u | static_cast<uint32_t>(local_row * bs * 8));
 }
 
+// Pencil layout of one sweep (k_sweep_pencil): a tile is a block of at most
+// rpc grid lines over their whole length, blocks of wy x wz lines in the
+// coordinates (y + skew*z, z) of the sweep, skew the smallest that makes
+// every dependency point to the same or an earlier block along both.  Tiles
+// are numbered in ticket order (every tile after the tiles it reads), a
+// tile's rows ordered by their level (Eq 4) and cut into chunks of up to rpc
+// rows of one level.  Every chunk has `width` dependency slots per row.
+// meta: per chunk pencil_meta_quads(width) planes of rpc x 4 words; the words
+// of a row are, two to a word, 16-bit byte offsets of its dependencies in the
+// tile's LDS -- the zero row at 0 (padding), the tile's own rows from
+// kPencilZeroBytes on (chunk i in slot i mod ring of 64 values), then the rows
+// fed from other tiles (the tile's e-th at place e mod ext_ring) -- and, in
+// word (width + 1) / 2, the fed rows the chunk needs.
+struct HostPencil {
+    bool tried = false;                    // the pattern was looked at
+    bool built = false;
+    int which = 0;
+    int rpc = 0;
+    int width = 0;
+    int wy = 0, wz = 0, skew = 0;
+    int ntiles = 0;
+    int nchunks = 0;
+    int next = 0;                          // fed rows
+    int ring = 0, ext_ring = 0;            // LDS places of own chunks and of fed rows
+    int reach = 0;                         // chunks a dependency inside a tile reaches back
+    int64_t nexch = 0;                     // rows in the exchange array
+    std::vector<int32_t> tile_ptr;         // [ntiles+1] first chunk
+    std::vector<int32_t> ext_ptr;          // [ntiles+1] first fed row
+    std::vector<int32_t> rows;             // [nchunks*rpc] block rows, -1 past a chunk's last row
+    std::vector<int32_t> entry;            // [nchunks*rpc] their exchange entries, -1: no other tile reads it
+    std::vector<int32_t> meta;             // [nchunks*pencil_meta_quads*rpc*4]
+    std::vector<int32_t> src;              // [nchunks*width*rpc] entry of P, -1 padding
+    std::vector<int32_t> ext_idx;          // [next] exchange entry
+    std::vector<int32_t> ext_free;         // [next] chunks finished before the place is free
+};
+
+constexpr int kPencilZeroBytes = 64;
+constexpr int kPencilSlotBytes = 512;      // 64 values of one column
+
+constexpr int kPencilRing = 24;            // ring slots: a multiple of every prefetch depth of the kernels
+constexpr int kPencilSlack = 18;           // chunks past the last that a prefetch may touch
+
+// Fed rows whose list is in LDS, a power of two: two halves, each longer than
+// the rpc rows that are looked at together.
+constexpr int pencil_list_rows(int rpc)
+{
+    int rows = 64;
+    while (rows < 4 * rpc) rows *= 2;
+    return rows;
+}
+
+constexpr int pencil_meta_quads(int width) { return ((width + 1) / 2 + 1 + 3) / 4; }
+
+// LDS of a workgroup that sweeps cb columns: zero row, ring and fed rows, then
+// the ring's destinations, the feeder's list and the place of values that are
+// not kept.
+inline int64_t pencil_lds_bytes(int ring, int ext_ring, int rpc, int bs, int cb)
+{
+    return static_cast<int64_t>(kPencilZeroBytes + ring * kPencilSlotBytes + ext_ring * bs * 8) * cb +
+           ring * kPencilSlotBytes + pencil_list_rows(rpc) * 16 + kPencilSlotBytes * cb;
+}
+
+// Dependency slots of the pencil kernels that exist for block size bs, the
+// smallest that holds max_width (0: none): 3, 6, 11 and 21 are the widest rows
+// of ILU(0..3) on a 7-point grid.  Two chunks of a row's factor values at least
+// stay in registers, which 21 slots of blocks above 4 x 4 do not.
+constexpr int pencil_width(int bs, int max_width)
+{
+    if (max_width <= 3) return 3;
+    if (max_width <= 6) return 6;
+    if (max_width <= 11) return 11;
+    if (max_width <= 21 && bs <= 4) return 21;
+    return 0;
+}
+// Widest rows for which two columns are swept together.
+constexpr int kPencilPairWidth = 6;
+
+struct DevPencil {
+    int32_t *tile_ptr = nullptr, *ext_ptr = nullptr, *rows = nullptr, *meta = nullptr, *src = nullptr,
+            *ext = nullptr;
+    char* recs = nullptr;                  // [nchunks + kPencilSlack] records (PencilRec)
+    size_t recs_bytes = 0;
+    int vals_precision = -1;
+    double* exch = nullptr;                // kNotReady between applications
+    size_t exch_cap = 0;
+};
+
 struct DevSweep {
     int64_t* chunk_off = nullptr;
     int32_t* rows = nullptr;
@@ -192,6 +279,7 @@ struct Host {
     HostSweep sweep[4];
     HostTiled tiled[4];
     HostTiled lines[4];     // line-sweep layouts (L and U' only; see build_line_layout)
+    HostPencil pencil[4];
 };
 
 // Host analysis entry points (analysis.cpp).
@@ -255,6 +343,21 @@ void build_line_layout(const Host& h, int which, int rpc, int ny_b, int nz_b, Ho
 // kernel reads, every neighbour either one step earlier in the block or in
 // an earlier block.
 int validate_line_layout(const Host& h, const HostTiled& s);
+// Dependencies of a sweep (factor entry and row read), by row, in ascending
+// column order.
+struct Dep {
+    int32_t col;
+    int64_t src;
+};
+void sweep_deps(const Host& h, int which, std::vector<int32_t>& ptr, std::vector<Dep>& deps);
+// Pencil layout of sweep `which` (pencil.cpp); out.built stays false where
+// the pattern has no grid lines, its rows are too wide for the kernels or
+// its dependencies reach too far for the LDS rings.
+void build_pencil(const Host& h, int which, int rpc, HostPencil& out);
+// Host self-check of a pencil layout: every row once, every dependency slot
+// decoded to the row its LDS place holds when it is read, every fed row from an
+// earlier tile and kept until its last reader, every index in range.
+int validate_pencil(const Host& h, const HostPencil& s);
 // Ticket order of the backward U' tiled sweep fused with the SpMV on its
 // output: all tiles, then each block of rpc rows of A, ordered by the tile
 // that finishes the lowest row the block reads.  Checked before it is

@@ -917,6 +917,76 @@ __global__ void k_layout_dinv_b(int64_t nrowslots, const int32_t* __restrict__ r
     }
 }
 
+// Records of a pencil layout (PencilRec): one wavefront per pair (FP64) or
+// quad (FP32) of values of a chunk, so its store is 1 KiB of consecutive
+// bytes, and one per plane of words.  Blocks formed as in k_layout_b.
+template <int B, typename T>
+__global__ __launch_bounds__(256) void k_layout_pencil(int64_t nchunks, int width, const int32_t* __restrict__ src,
+                                                       const int4* __restrict__ meta,
+                                                       const int32_t* __restrict__ Prow,
+                                                       const double* __restrict__ P, const double* __restrict__ Dinv,
+                                                       int upper, int transposed, char* __restrict__ recs)
+{
+    constexpr int BB = B * B;
+    constexpr int RPC = 64 / B;
+    constexpr int V = 16 / static_cast<int>(sizeof(T));       // values a lane stores together
+    const int kb = width * B;
+    const int left = kb % V;                                  // FP32: 2 and/or 1 values at the end
+    const int vunits = kb / V + (left >= 2 ? 1 : 0) + (left % 2);
+    const int w4 = pencil_meta_quads(width);
+    const int units = vunits + w4;
+    const int64_t rec_bytes = static_cast<int64_t>(kb) * 64 * sizeof(T) + static_cast<int64_t>(w4) * RPC * 16;
+    const int lane = lane_id();
+    const int q = lane / B;
+    const int r = lane - q * B;
+    const int64_t total = nchunks * units;
+    for (int64_t u = static_cast<int64_t>(blockIdx.x) * (blockDim.x / 64) + (threadIdx.x >> 6); u < total;
+         u += static_cast<int64_t>(gridDim.x) * (blockDim.x / 64)) {
+        const int64_t chunk = u / units;
+        const int p = static_cast<int>(u - chunk * units);
+        char* rec = recs + chunk * rec_bytes;
+        if (p >= vunits) {
+            int4* dst = reinterpret_cast<int4*>(rec + static_cast<int64_t>(kb) * 64 * sizeof(T)) + (p - vunits) * RPC;
+            if (lane < RPC) dst[lane] = meta[(chunk * w4 + (p - vunits)) * RPC + lane];
+            continue;
+        }
+        const int nv = p < kb / V ? V : p == kb / V && left >= 2 ? 2 : 1;
+        const int first = p < kb / V ? p * V : p == kb / V && left >= 2 ? kb / V * V : kb - 1;
+        T out[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const int j = first + e;
+            double v = 0.0;
+            if (e < nv && q < RPC) {
+                const int k = j / B;
+                const int c = j - k * B;
+                const int64_t sp = src[(chunk * width + k) * RPC + q];
+                if (sp >= 0) {
+                    const int fr = transposed ? c : r;
+                    const int fc = transposed ? r : c;
+                    if (!upper) {
+                        v = P[sp * BB + fc * B + fr];
+                    } else {
+                        const double* Di = Dinv + static_cast<int64_t>(Prow[sp]) * BB;
+                        const double* U = P + sp * BB;
+                        for (int m = 0; m < B; ++m) v += Di[m * B + fr] * U[fc * B + m];
+                    }
+                }
+            }
+            out[e] = static_cast<T>(v);
+        }
+        T* dst = reinterpret_cast<T*>(rec) + first * 64 + lane * nv;
+        if (nv == V) {
+            if constexpr (V == 2) *reinterpret_cast<double2*>(dst) = make_double2(out[0], out[1]);
+            else *reinterpret_cast<float4*>(dst) = make_float4(out[0], out[1], out[2], out[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (e < nv) dst[e] = out[e];
+        }
+    }
+}
+
 template <typename T>
 __global__ void k_layout_dinv(int64_t nrowslots, int B, int rpc, const int32_t* __restrict__ rows,
                               const double* __restrict__ Dinv, int transposed, T* __restrict__ out)

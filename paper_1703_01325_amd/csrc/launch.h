@@ -13,6 +13,9 @@
 #include "sweep_kernels.h"
 
 namespace bilu {
+namespace dev {
+struct PencilArgs;
+}
 namespace launch {
 
 // Level-chunk sweep (k_sweep): prec is a bilu_precision, rt the columns per
@@ -43,6 +46,11 @@ bool pairs(int kmax, int prec, bool fuse, int blocks, size_t lds, hipStream_t s,
 
 template <int B>
 bool lines(int prec, bool fuse, int blocks, hipStream_t s, const dev::LineArgs& a);
+
+// Pencil sweep (k_sweep_pencil): width a pencil_width(), cb columns per
+// workgroup (1, or 2 up to kPencilPairWidth), fuse: D^{-1} times the right-hand side is swept.
+template <int B>
+bool pencil(int width, int cb, int prec, bool fuse, int blocks, size_t lds, hipStream_t s, const dev::PencilArgs& a);
 
 // y = A x (trans = false) or A^T x, rt columns per pass (1, 4 or 8), or
 // rt = 0: lanes over the R columns (2 <= R <= 32); nothing runs when gate
