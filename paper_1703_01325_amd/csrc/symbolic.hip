@@ -8,15 +8,16 @@
 // level l exactly when the shortest path i -> ... -> j in the graph of A
 // (edge u -> v for every stored block (u, v)) whose inner vertices are all
 // below min(i, j) has l + 1 edges.  Every row is then independent of the
-// others.  One wavefront takes a row and runs k + 1 rounds of a
+// others.  A group of lanes takes a row and runs k + 1 rounds of a
 // Bellman-Ford search in the (min, max) semiring: M(v) is the smallest
 // possible largest inner vertex over the paths i -> v of at most L edges
 // whose inner vertices lie below i; a round extends by one edge the paths
 // ending in the vertices u < i whose M dropped in the round before
 // (M(v) <- min(M(v), max(M(u), u))), and v is kept with level L - 1 in the
 // first round where M(v) < min(i, v).  The visited vertices live in a hash
-// table in LDS (kHash slots; a row that reaches more than kHashFill
-// distinct vertices is refused).  A count pass sizes the rows, a scan gives
+// table in LDS, of a size for what rows of this k reach on grids; a row that
+// outgrows it is searched again in a larger one, and one that reaches more
+// than 3/4 kHash distinct vertices is refused.  A count pass sizes the rows, a scan gives
 // the row pointers and a write pass repeats the search and emits each row in
 // ascending column order (rank of each kept column among the row's).
 //
@@ -44,8 +45,7 @@
 
 namespace {
 
-constexpr int kHash = 1024;          // hash slots per row search
-constexpr int kHashFill = 768;       // distinct vertices a row search may reach
+constexpr int kHash = 1024;          // hash slots of the largest row search; it may reach 3/4 as many vertices
 constexpr unsigned short kKept = 0x8000u;
 constexpr unsigned int kSpinLimit = 1u << 20;
 
@@ -84,46 +84,70 @@ __global__ void k_check_ptr(int nb, const int32_t* __restrict__ Ap, int* status)
     if (blockIdx.x == 0 && threadIdx.x == 0 && Ap[0] != 0) atomicOr(status, kStPattern);
 }
 
+template <int SLOTS>
 struct RowTable {
-    int key[kHash];              // vertex, -1 empty
-    int mval[kHash];             // M after the last round
-    int mnext[kHash];            // running minimum of the candidates
-    unsigned short info[kHash];  // kKept | level
-    int list[kHash];             // frontier slots / kept slots
+    int key[SLOTS];              // vertex, -1 empty
+    int mval[SLOTS];             // M after the last round
+    int mnext[SLOTS];            // running minimum of the candidates
+    unsigned short info[SLOTS];  // kKept | level
+    unsigned short list[SLOTS];  // frontier slots / kept slots
     int nlist;
     int nused;
     int over;
 };
 
-__device__ __forceinline__ int table_slot(RowTable& t, int v)
+// log2 of a table size
+constexpr int slot_bits(int slots) { return slots <= 1 ? 0 : 1 + slot_bits(slots / 2); }
+
+template <int SLOTS>
+__device__ __forceinline__ int table_slot(RowTable<SLOTS>& t, int v)
 {
-    unsigned int h = (static_cast<unsigned int>(v) * 2654435761u) >> 22;   // 10 bits: kHash
-    for (int probe = 0; probe < kHash; ++probe) {
+    unsigned int h = (static_cast<unsigned int>(v) * 2654435761u) >> (32 - slot_bits(SLOTS));
+    for (int probe = 0; probe < SLOTS; ++probe) {
         const int old = atomicCAS(&t.key[h], -1, v);
         if (old == v) return static_cast<int>(h);
         if (old == -1) {
-            if (atomicAdd(&t.nused, 1) >= kHashFill) t.over = 1;
+            if (atomicAdd(&t.nused, 1) >= SLOTS / 4 * 3) t.over = 1;
             return static_cast<int>(h);
         }
-        h = (h + 1) & (kHash - 1);
+        h = (h + 1) & (SLOTS - 1);
     }
     t.over = 1;
     return -1;
 }
 
-// One wavefront per row.  WRITE = false: cnt[i] = kept entries of row i;
-// WRITE = true: row i written at Pp[i] in ascending columns.
-template <bool WRITE>
-__global__ __launch_bounds__(64) void k_sym_rows(int nb, const int32_t* __restrict__ Ap,
+// LANES lanes per row, 64 / LANES rows per wavefront, a table of SLOTS slots
+// each.  rows == nullptr: all nb rows, else the *nrows listed ones.  WRITE =
+// false: cnt[i] = kept entries of row i; WRITE = true: row i written at Pp[i]
+// in ascending columns.  A row that outgrows its table goes on the list
+// over_rows, or is refused if there is none.
+//
+// The searches wait on LDS and on the pattern's rows; what counts is how many
+// are in flight, and clearing and scanning the table is most of a small one's
+// work.  60x220x85, 7 points, k = 1: one row per wavefront in a table of 1024
+// slots (8 wavefronts fit a compute unit's LDS) took 5170 us to count and
+// 5630 us to write; four rows per wavefront in tables of 64 slots (32
+// wavefronts a compute unit) take 239 and 267 us.
+template <int SLOTS, int LANES, bool WRITE>
+__global__ __launch_bounds__(64) void k_sym_rows(int nb, const int32_t* __restrict__ rows,
+                                                 const int* __restrict__ nrows, const int32_t* __restrict__ Ap,
                                                  const int32_t* __restrict__ Aj, int k, int32_t* __restrict__ cnt,
                                                  const int32_t* __restrict__ Pp, int32_t* __restrict__ Pj,
-                                                 int32_t* __restrict__ Plev, int* status)
+                                                 int32_t* __restrict__ Plev, int32_t* __restrict__ over_rows,
+                                                 int* __restrict__ over_count, int* status)
 {
-    __shared__ RowTable t;
-    const int lane = threadIdx.x;
-    for (int i = blockIdx.x; i < nb; i += gridDim.x) {
+    constexpr int kRows = 64 / LANES;
+    constexpr int kEdges = 4;            // lanes along the row of one frontier vertex
+    __shared__ RowTable<SLOTS> table[kRows];
+    const int lane = threadIdx.x % LANES;
+    const int group = threadIdx.x / LANES;
+    RowTable<SLOTS>& t = table[group];
+    const int n = rows ? *nrows : nb;
+    for (int64_t q0 = static_cast<int64_t>(blockIdx.x) * kRows; q0 < n; q0 += static_cast<int64_t>(gridDim.x) * kRows) {
+        const bool live = q0 + group < n;
+        const int i = !live ? 0 : rows ? rows[q0 + group] : static_cast<int>(q0) + group;
         __syncthreads();
-        for (int s = lane; s < kHash; s += 64) {
+        for (int s = lane; s < SLOTS; s += LANES) {
             t.key[s] = -1;
             t.mval[s] = INT_MAX;
             t.mnext[s] = INT_MAX;
@@ -136,25 +160,28 @@ __global__ __launch_bounds__(64) void k_sym_rows(int nb, const int32_t* __restri
         }
         __syncthreads();
         // row i of A: level 0, no inner vertex (M = -1)
-        for (int e = Ap[i] + lane; e < Ap[i + 1]; e += 64) {
-            const int v = Aj[e];
-            const int s = table_slot(t, v);
-            if (s < 0) continue;
-            t.mval[s] = -1;
-            t.mnext[s] = -1;
-            t.info[s] = kKept;
-            if (v < i) t.list[atomicAdd(&t.nlist, 1)] = s;
+        if (live) {
+            for (int e = Ap[i] + lane; e < Ap[i + 1]; e += LANES) {
+                const int v = Aj[e];
+                const int s = table_slot(t, v);
+                if (s < 0) continue;
+                t.mval[s] = -1;
+                t.mnext[s] = -1;
+                t.info[s] = kKept;
+                if (v < i) t.list[atomicAdd(&t.nlist, 1)] = static_cast<unsigned short>(s);
+            }
         }
         __syncthreads();
         for (int L = 2; L <= k + 1; ++L) {
-            const int nf = t.nlist;
-            if (nf == 0 || t.over) break;
+            const int nf = t.over ? 0 : t.nlist;
+            if (!__any(nf)) break;
             // extend the paths ending in the frontier by one edge of A
-            for (int f = lane; f < nf; f += 64) {
+            for (int f = lane / kEdges; f < nf; f += LANES / kEdges) {
                 const int su = t.list[f];
                 const int u = t.key[su];
                 const int mu = max(t.mval[su], u);
-                for (int e = Ap[u]; e < Ap[u + 1]; ++e) {
+                const int e1 = Ap[u + 1];
+                for (int e = Ap[u] + lane % kEdges; e < e1; e += kEdges) {
                     const int s = table_slot(t, Aj[e]);
                     if (s >= 0) atomicMin(&t.mnext[s], mu);
                 }
@@ -163,44 +190,56 @@ __global__ __launch_bounds__(64) void k_sym_rows(int nb, const int32_t* __restri
             if (lane == 0) t.nlist = 0;
             __syncthreads();
             // fold the round in; the next frontier: vertices below i whose M dropped
-            for (int s = lane; s < kHash; s += 64) {
+            for (int s = lane; s < SLOTS; s += LANES) {
                 const int v = t.key[s];
                 if (v >= 0 && t.mnext[s] < t.mval[s]) {
                     const int m = t.mnext[s];
                     t.mval[s] = m;
                     if (!(t.info[s] & kKept) && m < min(i, v)) t.info[s] = static_cast<unsigned short>(kKept | (L - 1));
-                    if (v < i) t.list[atomicAdd(&t.nlist, 1)] = s;
+                    if (v < i) t.list[atomicAdd(&t.nlist, 1)] = static_cast<unsigned short>(s);
                 }
             }
             __syncthreads();
         }
-        if (t.over) {
-            if (lane == 0) atomicOr(status, kStTable);
-            continue;
+        const bool over = t.over != 0;
+        if (over && live && lane == 0) {
+            if (over_rows)
+                over_rows[atomicAdd(over_count, 1)] = i;
+            else
+                atomicOr(status, kStTable);
         }
         __syncthreads();
         if (lane == 0) t.nlist = 0;
         __syncthreads();
         // the kept entries: columns into mnext[], levels into mval[]
-        for (int s = lane; s < kHash; s += 64) {
-            if (t.key[s] >= 0 && (t.info[s] & kKept)) {
+        int col[SLOTS / LANES], lev[SLOTS / LANES];
+#pragma unroll
+        for (int u = 0; u < SLOTS / LANES; ++u) {
+            const int s = u * LANES + lane;
+            col[u] = (t.info[s] & kKept) ? t.key[s] : -1;
+            lev[u] = t.info[s] & 0xff;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < SLOTS / LANES; ++u) {
+            if (col[u] >= 0) {
                 const int q = atomicAdd(&t.nlist, 1);
-                t.mnext[q] = t.key[s];
-                t.mval[q] = t.info[s] & 0xff;
+                t.mnext[q] = col[u];
+                t.mval[q] = lev[u];
             }
         }
         __syncthreads();
-        const int nk = t.nlist;
+        const int nk = live && !over ? t.nlist : 0;
         if (!WRITE) {
-            if (lane == 0) cnt[i] = nk;
+            if (live && !over && lane == 0) cnt[i] = nk;
             continue;
         }
-        const int base = Pp[i];
-        for (int q = lane; q < nk; q += 64) {
-            const int col = t.mnext[q];
+        const int base = live ? Pp[i] : 0;
+        for (int q = lane; q < nk; q += LANES) {
+            const int c = t.mnext[q];
             int rank = 0;
-            for (int f = 0; f < nk; ++f) rank += t.mnext[f] < col;
-            Pj[base + rank] = col;
+            for (int f = 0; f < nk; ++f) rank += t.mnext[f] < c;
+            Pj[base + rank] = c;
             Plev[base + rank] = t.mval[q];
         }
     }
@@ -224,20 +263,35 @@ __device__ __forceinline__ void coherent_store_i(int* p, int v)
 
 // Level of every row (Eq 4) for one sweep.  Row r reads the rows idx[e],
 // e in [ptr[r], ptr[r+1]) that pass the filter: mode 0 below r, mode 1
-// above r, mode 2 all.  forward: sweep order is ascending rows.  A lane
-// keeps a cursor into its row's list and the deepest level seen so far, so
-// a dependency found published is never read again; a dependency on a row
-// of the same wavefront is read from LDS, where the wavefront keeps its
-// rows' levels, so chains inside the wavefront advance without a round
-// trip through memory.  Global polls sleep between rounds only when no lane
-// of the wavefront made progress.
-__global__ __launch_bounds__(256) void k_levels(int nb, const int32_t* __restrict__ ptr,
-                                                const int32_t* __restrict__ idx, int mode, int forward, int* lvl,
-                                                unsigned int* ticket, int* status)
+// above r, mode 2 all.  forward: sweep order is ascending rows.
+//
+// A chain of dependent rows: what counts is the time from a level's store to
+// the store of the level above it.  So a lane lists the rows it reads in LDS
+// before it waits (the far ones first) and holds the next kLevelSlots of
+// them in registers; a round loads the levels of all of those that are still
+// pending at once; a dependency on a row of the same wavefront is read from
+// LDS, and chains inside the wavefront advance there without a round trip
+// through memory.  A dependency found published is never read again.  On a
+// grid numbered line by line the rows held by running wavefronts are the
+// window in which the chains of different lines overlap: 16 wavefronts a
+// compute unit; 12 lose to the window, 32 to each other's polls.  Wavefronts
+// in which nothing moved sleep between rounds.
+// Level sets of L on 60x220x85, 7 points, in ms: k = 0, 1, 2 (363, 750 and
+// 1305 levels) 6.5, 13.4 and 24.5 with the lists read again from memory in
+// every round by 8 wavefronts a compute unit, 1.6, 2.4 and 3.6 so; with 8
+// wavefronts of this kernel 2.4, 3.6 and 5.5, with 32 2.0, 3.4 and 5.5.
+constexpr int kLevelSlots = 12;      // rows polled at once
+constexpr int kLevelStage = 32;      // rows listed before the first wait
+
+__global__ __launch_bounds__(256, 4) void k_levels(int nb, const int32_t* __restrict__ ptr,
+                                                   const int32_t* __restrict__ idx, int mode, int forward, int* lvl,
+                                                   unsigned int* ticket, int* status)
 {
     __shared__ int wl[4][64];
+    __shared__ int wstage[4][kLevelStage][64];
     const int lane = threadIdx.x & 63;
     int* mine = wl[threadIdx.x >> 6];
+    int (*stage)[64] = wstage[threadIdx.x >> 6];
     for (;;) {
         unsigned int tk = 0;
         if (lane == 0) tk = atomicAdd(ticket, 1u);
@@ -248,64 +302,110 @@ __global__ __launch_bounds__(256) void k_levels(int nb, const int32_t* __restric
         const int row = pos < nb ? (forward ? pos : nb - 1 - pos) : -1;
         bool done = row < 0;
         mine[lane] = -1;
-        __builtin_amdgcn_wave_barrier();
         int e = done ? 0 : ptr[row];
         const int e1 = done ? 0 : ptr[row + 1];
+        const int ends = e + e1 - 1;
         int best = -1;
-        // Advances the lane's cursor past every dependency found published;
-        // with allow_global false only rows of this wavefront are read (LDS)
-        // and a dependency on another wavefront's row stops the cursor.
-        auto advance = [&](bool allow_global) {
-            bool moved = false;
-            if (done) return false;
-            bool blocked = false;
-            while (!blocked && e < e1) {
-                int lv[4];
+        int dep[kLevelSlots];          // a row of another wavefront, or a lane of this one
+        unsigned int pend = 0, local = 0, slots = 0;
+        int staged = 0, taken = 0;
+        // the next entries that pass, into the stage
+        auto fetch = [&]() {
+            staged = taken = 0;
+            while (e < e1 && staged < kLevelStage) {
+                int j[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int j = e + u < e1 ? idx[e + u] : row;
-                    const bool use = mode == 2 ? (e + u < e1) : mode == 0 ? (j < row) : (j > row);
-                    const int pj = forward ? j : nb - 1 - j;
-                    const bool local = pj >= pos0 && pj < pos0 + 64;
-                    lv[u] = !use ? INT_MIN : local ? mine[pj - pos0] : allow_global ? coherent_load_i(lvl + j) : -1;
+                    const int at = min(e + u, e1 - 1);
+                    j[u] = idx[forward ? at : ends - at];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    if (!blocked && e < e1) {
-                        if (lv[u] == -1) {
-                            blocked = true;
-                        } else {
-                            best = max(best, lv[u]);
-                            ++e;
-                            moved = true;
-                        }
+                    if (e < e1 && staged < kLevelStage) {
+                        if (mode == 2 || (mode == 0 ? j[u] < row : j[u] > row)) stage[staged++][lane] = j[u];
+                        ++e;
                     }
                 }
             }
-            if (!blocked) {
-                mine[lane] = best + 1;
-                coherent_store_i(lvl + row, best + 1);
-                done = true;
-                moved = true;
-            }
-            return moved;
         };
+        // the next of the stage, into registers
+        auto refill = [&]() {
+            if (taken == staged && e < e1) fetch();
+            const int c = min(staged - taken, kLevelSlots);
+            pend = (1u << c) - 1u;
+            local = 0;
+#pragma unroll
+            for (int u = 0; u < kLevelSlots; ++u) {
+                const int j = u < c ? stage[taken + u][lane] : 0;
+                const int l = (forward ? j : nb - 1 - j) - pos0;
+                const bool in = u < c && l >= 0 && l < 64;
+                dep[u] = in ? l : j;
+                if (in) local |= 1u << u;
+            }
+            taken += c;
+        };
+        if (!done) refill();
         unsigned int spins = 0;
-        while (!__all(done)) {
-            bool moved = advance(true);
-            // chains inside the wavefront: LDS only, until nothing moves
+        bool fresh = true;
+        for (;;) {
+            bool moved = false;
+            // rows of other wavefronts: every pending level at once
+            int lv[kLevelSlots];
+            const unsigned int far = pend & ~local;
+#pragma unroll
+            for (int u = 0; u < kLevelSlots; ++u) lv[u] = (far >> u & 1u) ? coherent_load_i(lvl + dep[u]) : -1;
+#pragma unroll
+            for (int u = 0; u < kLevelSlots; ++u) {
+                if (lv[u] != -1) {
+                    best = max(best, lv[u]);
+                    pend &= ~(1u << u);
+                    moved = true;
+                }
+            }
+            // rows of this one, until nothing moves
             for (;;) {
+                if (fresh) {
+                    slots = 0;
+#pragma unroll
+                    for (int u = 0; u < kLevelSlots; ++u) slots |= __any(local >> u & 1u) ? 1u << u : 0u;
+                    fresh = false;
+                }
+#pragma unroll
+                for (int u = 0; u < kLevelSlots; ++u) {
+                    if (slots >> u & 1u) {
+                        const int l = (pend & local) >> u & 1u ? mine[dep[u]] : -1;
+                        if (l != -1) {
+                            best = max(best, l);
+                            pend &= ~(1u << u);
+                        }
+                    }
+                }
+                bool step = false;
+                if (!done && pend == 0) {
+                    if (taken < staged || e < e1) {
+                        refill();
+                        fresh = true;
+                    }
+                    if (pend == 0) {
+                        mine[lane] = best + 1;
+                        coherent_store_i(lvl + row, best + 1);
+                        done = true;
+                    }
+                    step = true;
+                }
+                fresh = __any(fresh);
+                if (!__any(step)) break;
+                moved = true;
                 __builtin_amdgcn_wave_barrier();
                 asm volatile("" ::: "memory");
-                if (!__any(advance(false))) break;
-                moved = true;
             }
-            if (!__any(moved) && !__all(done)) {
+            if (__all(done)) break;
+            if (!__any(moved)) {
                 if (++spins > kSpinLimit) {
                     atomicOr(status, kStTimeout);
                     return;
                 }
-                __builtin_amdgcn_s_sleep(2);
+                __builtin_amdgcn_s_sleep(8);
             }
         }
     }
@@ -377,8 +477,6 @@ int grid_for(int64_t n, int threads, int cap = 4096)
     return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((n + threads - 1) / threads, cap)));
 }
 
-int rows_grid(int nb) { return std::min(nb, 65536); }
-
 bilu_status status_to_error(int st)
 {
     if (st & kStTimeout) return BILU_ERR_TIMEOUT;
@@ -392,6 +490,32 @@ bilu_status status_to_error(int st)
     do {                                                \
         if ((call) != hipSuccess) return BILU_ERR_HIP; \
     } while (0)
+
+// Searches all rows: first in tables for what a row of this k reaches on a
+// 7-point grid (19, 43, 86 and 151 vertices for k = 1 to 4; a table takes 3/4
+// of its slots), the rows that outgrow them in larger ones.
+template <bool WRITE>
+bilu_status search_rows(int nb, const int32_t* Ap, const int32_t* Aj, int k, int32_t* cnt, const int32_t* Pp,
+                        int32_t* Pj, int32_t* Plev, int* d_status, Scratch& sc, hipStream_t s)
+{
+    int* over = sc.get<int>(2);                                    // lengths of the two lists
+    int32_t* list1 = sc.get<int32_t>(static_cast<size_t>(nb));
+    int32_t* list2 = sc.get<int32_t>(static_cast<size_t>(nb));
+    if (!over || !list1 || !list2) return BILU_ERR_ALLOC;
+    CKH(hipMemsetAsync(over, 0, 2 * sizeof(int), s));
+    const auto grid = [nb](int rows) { return std::min((nb + rows - 1) / rows, 65536); };
+    if (k <= 2)
+        k_sym_rows<64, 16, WRITE><<<grid(4), 64, 0, s>>>(nb, nullptr, nullptr, Ap, Aj, k, cnt, Pp, Pj, Plev, list1,
+                                                         over, d_status);
+    else
+        k_sym_rows<128, 32, WRITE><<<grid(2), 64, 0, s>>>(nb, nullptr, nullptr, Ap, Aj, k, cnt, Pp, Pj, Plev, list1,
+                                                          over, d_status);
+    k_sym_rows<256, 64, WRITE><<<std::min(nb, 8192), 64, 0, s>>>(nb, list1, over, Ap, Aj, k, cnt, Pp, Pj, Plev, list2,
+                                                                 over + 1, d_status);
+    k_sym_rows<kHash, 64, WRITE><<<std::min(nb, 2048), 64, 0, s>>>(nb, list2, over + 1, Ap, Aj, k, cnt, Pp, Pj, Plev,
+                                                                   nullptr, nullptr, d_status);
+    return BILU_OK;
+}
 
 // Checks the pattern, sizes the rows and writes the row pointers; *nnzb
 // receives the entry count.
@@ -410,7 +534,8 @@ bilu_status sym_count(int nb, const int32_t* Ap, const int32_t* Aj, int k, int32
     CKH(hipMemcpyAsync(&h_status, d_status, sizeof(int), hipMemcpyDeviceToHost, s));
     CKH(hipStreamSynchronize(s));
     if (h_status) return status_to_error(h_status);
-    k_sym_rows<false><<<rows_grid(nb), 64, 0, s>>>(nb, Ap, Aj, k, cnt, nullptr, nullptr, nullptr, d_status);
+    const bilu_status st = search_rows<false>(nb, Ap, Aj, k, cnt, nullptr, nullptr, nullptr, d_status, sc, s);
+    if (st != BILU_OK) return st;
     size_t tmp_bytes = 0;
     if (rocprim::exclusive_scan(nullptr, tmp_bytes, cnt, ptr64, int64_t(0), static_cast<size_t>(nb) + 1,
                                 rocprim::plus<int64_t>(), s) != hipSuccess)
@@ -440,7 +565,8 @@ bilu_status sym_write(int nb, const int32_t* Ap, const int32_t* Aj, int k, const
     int* d_status = sc.get<int>(1);
     if (!d_status) return BILU_ERR_ALLOC;
     CKH(hipMemsetAsync(d_status, 0, sizeof(int), s));
-    k_sym_rows<true><<<rows_grid(nb), 64, 0, s>>>(nb, Ap, Aj, k, nullptr, Pp, Pj, Plev, d_status);
+    const bilu_status st = search_rows<true>(nb, Ap, Aj, k, nullptr, Pp, Pj, Plev, d_status, sc, s);
+    if (st != BILU_OK) return st;
     int h_status = 0;
     CKH(hipMemcpyAsync(&h_status, d_status, sizeof(int), hipMemcpyDeviceToHost, s));
     CKH(hipStreamSynchronize(s));
@@ -493,7 +619,7 @@ bilu_status levels_impl(int nb, const int32_t* Pp, const int32_t* Pj, int sweep,
     }
     // persistent: at most as many wavefronts as there are row groups
     const int groups = static_cast<int>((static_cast<int64_t>(nb) + 63) / 64);
-    const int wg = std::max(1, std::min((groups + 3) / 4, 512));
+    const int wg = std::max(1, std::min((groups + 3) / 4, 1024));
     k_levels<<<wg, 256, 0, s>>>(nb, ptr, idx, mode, forward ? 1 : 0, lvl,
                                 reinterpret_cast<unsigned int*>(d_small + 2), d_small);
     int32_t* rows_in = sc.get<int32_t>(static_cast<size_t>(nb));
