@@ -55,6 +55,7 @@ def build(verbose: bool = False) -> str:
         hip_job("sweep_b.hip", f"sweep_b{b}.o", f"-DBILU_B={b}")
         hip_job("pencil_b.hip", f"pencil_b{b}.o", f"-DBILU_B={b}")
     hip_job("batch_sweep.hip", "batch_sweep.o")
+    hip_job("pencil_batch.hip", "pencil_batch.o")
     hip_job("symbolic.hip", "symbolic.o")
     for name in ("analysis", "pencil"):
         objs.append(os.path.join(OUT_DIR, f"{name}.o"))

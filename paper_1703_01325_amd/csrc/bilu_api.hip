@@ -143,7 +143,6 @@ struct bilu_ctx {
     DevPencil pencil[4];
     double* d_pw = nullptr;
     size_t pw_cap = 0;
-    bool pencil_off = false;
 
     double* d_y = nullptr;      // intermediate of an application, kept at kNotReady
     size_t y_cap = 0;
@@ -863,7 +862,7 @@ bilu_status layout_form(bilu_ctx* c, int form, hipStream_t s)
 // 7 times, figures at k_sweep_pencil), so there is no other condition.
 bool pencil_wanted(const bilu_ctx* c)
 {
-    return !c->pencil_off && !c->values_only && c->sweep_mode == 2 && c->h.bs <= kMaxKernelBs &&
+    return !c->values_only && c->sweep_mode == 2 && c->h.bs <= kMaxKernelBs &&
            c->tile_rows_req == 0 && c->tile_group_req == 0 && c->tile_block == 0 && c->line_block == 0 &&
            c->helper == 0 && c->rhs_pairs == 0 && c->split_dinv == 0 && !c->fuse_spmv && c->blocks_override == 0;
 }

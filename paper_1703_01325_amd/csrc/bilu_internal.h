@@ -191,6 +191,7 @@ struct HostPencil {
     std::vector<int32_t> ext_free;         // [next] chunks finished before the place is free
 };
 
+constexpr int kPencilBatchWidth = 3;       // width of the batch kernel
 constexpr int kPencilZeroBytes = 64;
 constexpr int kPencilSlotBytes = 512;      // 64 values of one column
 

@@ -15,6 +15,7 @@
 namespace bilu {
 namespace dev {
 struct PencilArgs;
+struct PencilBatchArgs;
 }
 namespace launch {
 
@@ -63,6 +64,9 @@ bool spmv(int rt, bool trans, int nb, const int32_t* rp, const int32_t* cj, cons
 // Batch sweep over the members' tiled layouts (every block size in one
 // kernel); fuse: the second sweep of an application (D^{-1} fused).
 bool batch_sweep(bool fp32, bool fuse, int blocks, size_t lds, hipStream_t s, const dev::BatchSweepArgs& a);
+
+// The same over the members' pencil layouts, all of width kPencilBatchWidth.
+bool pencil_batch(bool fp32, bool fuse, int blocks, size_t lds, hipStream_t s, const dev::PencilBatchArgs& a);
 
 }  // namespace launch
 }  // namespace bilu

@@ -620,30 +620,64 @@ __device__ __forceinline__ void pencil_store(const PencilArgs& a, int t, int cg,
     }
 }
 
+// LDS of a workgroup; swept, count: its counters.
+template <int B, int CB>
+__device__ __forceinline__ PencilLds pencil_lds_map(const PencilArgs& a, char* base, int* swept, int* count)
+{
+    PencilLds l;
+    l.base = base;
+    l.ring = l.base + kPencilZeroBytes * CB;
+    l.ext = l.ring + a.ring * kPencilSlotBytes * CB;
+    l.dest = l.ext + a.ext_ring * (B * 8 * CB);
+    l.list = reinterpret_cast<int4*>(l.dest + a.ring * 512);
+    l.swept = swept;
+    l.listed = count;
+    l.staged = count + 1;
+    l.stored = count + 2;
+    l.fed = count + 3;
+    return l;
+}
+
+// no destination of a slot yet: a wait that expires lets the storer pass
+// slots that were never staged
+__device__ __forceinline__ void pencil_clear_dest(const PencilArgs& a, const PencilLds& l)
+{
+    for (int i = static_cast<int>(threadIdx.x); i < a.ring * 128; i += 256)
+        reinterpret_cast<uint32_t*>(l.dest)[i] = kNowhere;
+}
+
+// Tile t for column group cg, by the four wavefronts; part / parts: its share
+// of the reset of the other sweep's exchange array.
+template <int B, typename T, int K, int CB, bool FUSE>
+__device__ __forceinline__ void pencil_tile(const PencilArgs& a, int t, int cg, int part, int parts,
+                                            const PencilLds& l, int wave)
+{
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);
+        pencil_sweep<B, T, K, CB>(a, t, l);
+        __builtin_amdgcn_s_setprio(0);
+    } else if (wave == 1) {
+        pencil_feed<B, CB>(a, t, cg, l);
+        const int64_t lo = a.nreset * part / parts, hi = a.nreset * (part + 1) / parts;
+        for (int64_t i = lo + lane_id(); i < hi; i += 64) a.reset[i] = not_ready();
+    } else if (wave == 2) {
+        pencil_stage<B, CB, FUSE, sizeof(T) == 4>(a, t, cg, l);
+    } else {
+        pencil_store<B, CB>(a, t, cg, l);
+    }
+}
+
 template <int B, typename T, int K, int CB, bool FUSE>
 __global__ __launch_bounds__(256, (PencilRec<B, T, K>::waves(CB))) void k_sweep_pencil(PencilArgs a)
 {
     extern __shared__ double2 pencil_lds[];
     __shared__ int s_swept[64], s_count[5];
     if (gated_off(a.gate)) return;
-    PencilLds l;
-    l.base = reinterpret_cast<char*>(pencil_lds);
-    l.ring = l.base + kPencilZeroBytes * CB;
-    l.ext = l.ring + a.ring * kPencilSlotBytes * CB;
-    l.dest = l.ext + a.ext_ring * (B * 8 * CB);
-    l.list = reinterpret_cast<int4*>(l.dest + a.ring * 512);
-    l.swept = s_swept;
-    l.listed = s_count;
-    l.staged = s_count + 1;
-    l.stored = s_count + 2;
-    l.fed = s_count + 3;
+    const PencilLds l = pencil_lds_map<B, CB>(a, reinterpret_cast<char*>(pencil_lds), s_swept, s_count);
     int& s_ticket = s_count[4];
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     if (static_cast<int>(threadIdx.x) < kPencilZeroBytes / 8 * CB) reinterpret_cast<double*>(l.base)[threadIdx.x] = 0.0;
-    // no destination of a slot yet: a wait that expires lets the storer pass
-    // slots that were never staged
-    for (int i = static_cast<int>(threadIdx.x); i < a.ring * 128; i += 256)
-        reinterpret_cast<uint32_t*>(l.dest)[i] = kNowhere;
+    pencil_clear_dest(a, l);
     const int nticket = a.ntiles * a.ncg;
     for (;;) {
         if (threadIdx.x < 64) s_swept[threadIdx.x] = 0;
@@ -657,23 +691,93 @@ __global__ __launch_bounds__(256, (PencilRec<B, T, K>::waves(CB))) void k_sweep_
         if (tk >= nticket) break;
         const int t = tk / a.ncg;
         const int cg = tk - t * a.ncg;
-        if (wave == 0) {
-            __builtin_amdgcn_s_setprio(3);
-            pencil_sweep<B, T, K, CB>(a, t, l);
-            __builtin_amdgcn_s_setprio(0);
-        } else if (wave == 1) {
-            pencil_feed<B, CB>(a, t, cg, l);
-            // this ticket's share of the other sweep's exchange array
-            const int64_t lo = a.nreset * tk / nticket, hi = a.nreset * (tk + 1) / nticket;
-            for (int64_t i = lo + lane_id(); i < hi; i += 64) a.reset[i] = not_ready();
-        } else if (wave == 2) {
-            pencil_stage<B, CB, FUSE, sizeof(T) == 4>(a, t, cg, l);
-        } else {
-            pencil_store<B, CB>(a, t, cg, l);
-        }
+        pencil_tile<B, T, K, CB, FUSE>(a, t, cg, tk, nticket, l, wave);
         __syncthreads();
     }
     if (wave == 0) finish_persistent(a.ticket, a.done, a.total_waves);
+}
+
+// ---------------------------------------------------------------------------
+// The same over a batch: tickets are (member, tile) pairs, each member with
+// arguments of its own in device memory.  One kernel holds every block size
+// at the width of ILU(0) on a grid (kPencilBatchWidth): their registers all
+// allow two workgroups per compute unit, which wider rows would halve.
+// One application of 64 systems of 8 to 40 cells a side, blocks of 2 to 8
+// (1.3 GB of factors and vectors, 280 us at the rate of a copy): 1144 us with
+// a wavefront a row tile (k_sweep_batch), 467 us so.
+// ---------------------------------------------------------------------------
+struct PencilMember {
+    PencilArgs a;              // rhs, out, ticket, done, status, gate unset
+    int64_t voff;              // first unknown of the member in the batch vectors
+    int bs;
+    int pad;
+};
+
+struct PencilBatchArgs {
+    const PencilMember* mem;
+    const int2* items;         // (member, tile)
+    int nitems;
+    const double* rhs;
+    double* out;
+    const int* active;         // per member, or null: every member
+    const int* gate;           // nothing runs when given and *gate == 0
+    unsigned long long* ticket;
+    unsigned int* done;
+    int* status;
+    unsigned int total_waves;  // workgroups launched
+    unsigned int spin_limit;
+};
+
+template <int B, typename T, bool FUSE>
+__device__ __forceinline__ void pencil_batch_tile(const PencilArgs& a, int t, char* base, int* swept, int* count,
+                                                  int wave)
+{
+    const PencilLds l = pencil_lds_map<B, 1>(a, base, swept, count);
+    // the LDS held another member's tile
+    pencil_clear_dest(a, l);
+    __syncthreads();
+    pencil_tile<B, T, kPencilBatchWidth, 1, FUSE>(a, t, 0, t, a.ntiles, l, wave);
+    __syncthreads();
+}
+
+template <typename T, bool FUSE>
+__global__ __launch_bounds__(256, 2) void k_sweep_pencil_batch(PencilBatchArgs b)
+{
+    extern __shared__ double2 pencil_lds[];
+    __shared__ int s_swept[64], s_count[5];
+    if (gated_off(b.gate)) return;
+    char* base = reinterpret_cast<char*>(pencil_lds);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    if (static_cast<int>(threadIdx.x) < kPencilZeroBytes / 8) reinterpret_cast<double*>(base)[threadIdx.x] = 0.0;
+    for (;;) {
+        if (threadIdx.x < 64) s_swept[threadIdx.x] = 0;
+        if (threadIdx.x == 0) {
+            const unsigned long long tk = atomicAdd(b.ticket, 1ULL);
+            for (int i = 0; i < 4; ++i) s_count[i] = 0;
+            s_count[4] = tk > 0x3fffffffULL ? 0x3fffffff : static_cast<int>(tk);
+        }
+        __syncthreads();
+        const int tk = __builtin_amdgcn_readfirstlane(s_count[4]);
+        // (the ticket is read by every wavefront before it is drawn again)
+        __syncthreads();
+        if (tk >= b.nitems) break;
+        const int2 it = uniform_record(b.items, tk);
+        if (b.active && !uniform_load(b.active, it.x)) continue;
+        PencilMember m = uniform_record(b.mem, it.x);
+        m.a.rhs = b.rhs + m.voff;
+        m.a.out = b.out + m.voff;
+        m.a.status = b.status;
+        m.a.spin_limit = b.spin_limit;
+        switch (m.bs) {
+#define BILU_PENCIL_BATCH(BS) \
+    case BS: pencil_batch_tile<BS, T, FUSE>(m.a, it.y, base, s_swept, s_count, wave); break;
+        BILU_PENCIL_BATCH(1) BILU_PENCIL_BATCH(2) BILU_PENCIL_BATCH(3) BILU_PENCIL_BATCH(4)
+        BILU_PENCIL_BATCH(5) BILU_PENCIL_BATCH(6) BILU_PENCIL_BATCH(7) BILU_PENCIL_BATCH(8)
+#undef BILU_PENCIL_BATCH
+        default: break;
+        }
+    }
+    if (wave == 0) finish_persistent(b.ticket, b.done, b.total_waves);
 }
 
 }  // namespace dev
