@@ -375,11 +375,57 @@ __device__ __forceinline__ bool gather(double* dst, int n, int t, Load load)
         asm volatile("" ::: "memory");        \
     } while (0)
 
+// Inverse of a b x b block held by b*b consecutive lanes from `base` on, lane
+// base + c*b + r element (r, c), by Gauss-Jordan with partial pivoting: the
+// operations of the LDS form in k_factor_rows_lds in their order, every
+// element in its lane's registers.  bad: a pivot was zero or not finite.
+// (A row's inverse is on the chain from level to level; through LDS, with a
+// wavefront-level wait after each of its nine steps a column, it took more than
+// half of a row's time.)
+template <int B>
+__device__ __forceinline__ double block_inverse(double w, int r, int c, int base, bool& bad)
+{
+    double e = r == c ? 1.0 : 0.0;
+#pragma unroll
+    for (int col = 0; col < B; ++col) {
+        double v[B];
+#pragma unroll
+        for (int rr = col; rr < B; ++rr) v[rr] = __shfl(w, base + col * B + rr);
+        int piv = col;
+        double best = fabs(v[col]), dd = v[col];
+#pragma unroll
+        for (int rr = col + 1; rr < B; ++rr) {
+            const double m = fabs(v[rr]);
+            if (m > best) {
+                best = m;
+                piv = rr;
+                dd = v[rr];
+            }
+        }
+        bad |= !(best > 0.0) || !isfinite(best);
+        if (__any(piv != col)) {
+            const int from = base + c * B + (r == col ? piv : r == piv ? col : r);
+            w = __shfl(w, from);
+            e = __shfl(e, from);
+        }
+        const double pw = __shfl(w, base + c * B + col) / dd;
+        const double pe = __shfl(e, base + c * B + col) / dd;
+        const double f = __shfl(w, base + col * B + r);
+        if (r == col) {
+            w = pw;
+            e = pe;
+        } else {
+            w -= f * pw;
+            e -= f * pe;
+        }
+    }
+    return e;
+}
+
 template <int B, int NWV>
 __global__ __launch_bounds__(64 * NWV) void k_factor_waves(FactorWaveArgs a)
 {
     constexpr int BB = B * B;
-    constexpr int W = 2 * B;
     constexpr int kPairs = 64 / BB > 0 ? 64 / BB : 1;
     // loads in flight per lane while a row is staged: eight for b >= 4 (rows of
     // many blocks; Poisson 120^3 b = 8, k = 3 214 -> 160 ms), one below, where
@@ -387,9 +433,6 @@ __global__ __launch_bounds__(64 * NWV) void k_factor_waves(FactorWaveArgs a)
     // with eight against 2.06)
     constexpr int kG = B >= 4 ? 8 : 1;
     extern __shared__ double fw[];
-    __shared__ double sWall[NWV][B * W];
-    __shared__ int sPivAll[NWV];
-    __shared__ int sBadAll[NWV];
     __shared__ unsigned int sTk;
     const int wave = static_cast<int>(threadIdx.x) >> 6;
     const int t = lane_id();
@@ -399,9 +442,6 @@ __global__ __launch_bounds__(64 * NWV) void k_factor_waves(FactorWaveArgs a)
     const int el = t - sub * BB;
     const int er = el % B;
     const int ec = el / B;
-    double* sW = sWall[wave];
-    int& sPiv = sPivAll[wave];
-    int& sBad = sBadAll[wave];
     double* mine = fw + static_cast<int64_t>(wave) * (a.lds_per_wave / 8);
     for (;;) {
         __syncthreads();
@@ -426,7 +466,6 @@ __global__ __launch_bounds__(64 * NWV) void k_factor_waves(FactorWaveArgs a)
             int* sF = sQ + dk + 1;
             int* sG = sF + npair;
             int* sPv = sG + npair;
-            if (t == 0) sBad = 0;
             gather<kG>(sRow, nrow * BB, t, [&](int y) {
                 const int k = y / BB;
                 const int32_t src = a.PtoA[e0 + k];
@@ -507,60 +546,12 @@ __global__ __launch_bounds__(64 * NWV) void k_factor_waves(FactorWaveArgs a)
                 }
                 k0 = k1;
             }
-            if (t < BB) {
-                sW[r * W + c] = sRow[dk * BB + t];
-                sW[r * W + B + c] = (r == c) ? 1.0 : 0.0;
-            }
             for (int y = t; y < nrow * BB; y += 64)
                 coherent_store(a.P + static_cast<int64_t>(e0) * BB + y, publishable(sRow[y]));
-            BILU_WAVE_SYNC();
-            for (int col = 0; col < B; ++col) {
-                if (t == 0) {
-                    int piv = col;
-                    double best = fabs(sW[col * W + col]);
-                    for (int rr = col + 1; rr < B; ++rr) {
-                        const double v = fabs(sW[rr * W + col]);
-                        if (v > best) {
-                            best = v;
-                            piv = rr;
-                        }
-                    }
-                    if (!(best > 0.0) || !isfinite(best)) sBad = 1;
-                    sPiv = piv;
-                }
-                BILU_WAVE_SYNC();
-                const int piv = sPiv;
-                if (piv != col && t < W) {
-                    const double tmp = sW[col * W + t];
-                    sW[col * W + t] = sW[piv * W + t];
-                    sW[piv * W + t] = tmp;
-                }
-                BILU_WAVE_SYNC();
-                const double dd = sW[col * W + col];
-                BILU_WAVE_SYNC();
-                if (t < W) sW[col * W + t] /= dd;
-                BILU_WAVE_SYNC();
-                double fct[2];
-#pragma unroll
-                for (int s2 = 0; s2 < 2; ++s2) {
-                    const int idx = t + 64 * s2;
-                    fct[s2] = idx < B * W ? sW[(idx / W) * W + col] : 0.0;
-                }
-                BILU_WAVE_SYNC();
-#pragma unroll
-                for (int s2 = 0; s2 < 2; ++s2) {
-                    const int idx = t + 64 * s2;
-                    if (idx < B * W) {
-                        const int rr = idx / W;
-                        const int cc = idx - rr * W;
-                        if (rr != col) sW[idx] -= fct[s2] * sW[col * W + cc];
-                    }
-                }
-                BILU_WAVE_SYNC();
-            }
-            if (t < BB)
-                coherent_store(a.Dinv + static_cast<int64_t>(i) * BB + t, publishable(sW[r * W + B + c]));
-            if (t == 0 && sBad) atomicMin(a.bad_row, i);
+            bool bad = false;
+            const double inv = block_inverse<B>(t < BB ? sRow[dk * BB + t] : 0.0, r, c, 0, bad);
+            if (t < BB) coherent_store(a.Dinv + static_cast<int64_t>(i) * BB + t, publishable(inv));
+            if (t == 0 && bad) atomicMin(a.bad_row, i);
             BILU_WAVE_SYNC();
         }
     }
