@@ -1069,6 +1069,7 @@ int analyze_host(Host& h, int nb, int bs, const int32_t* Ap, const int32_t* Aj, 
         for (int32_t e = h.Pp[i]; e < h.Pp[i + 1]; ++e) {
             h.Prow[e] = i;
             if (h.Pj[e] == i) h.Pdiag[i] = e;
+            h.nnz_lower += h.Pj[e] < i;
         }
     // A's blocks inside P (Algorithm 5, backfill): both rows are sorted.
     h.AtoP.resize(h.Aj.size());

@@ -85,7 +85,7 @@ struct bilu_ctx {
     bool dev_ready = false;
     bool factored = false;
     bool split_done = false;
-    mutable bool f_ready = false; // d_F holds the split factors of the current factorisation
+    bool f_ready = false; // d_F (allocated for the point view) holds the split factors of the current factorisation
     int precision = BILU_FACTORS_FP64;
     int sweep_mode = 2;
     int tile_rows = 0;          // rows per tile of the tiled layouts (0: not chosen yet)
@@ -535,17 +535,17 @@ bool launch_factor_waves(bilu_ctx* c, const double* Ax, hipStream_t s)
     BILU_SWITCH_B(c->h.bs, hipLaunchKernelGGL((dev::k_factor_waves<B, 1>), dim3(blocks), dim3(64), lds, s, a))
 }
 
-bool launch_split(const bilu_ctx* c, hipStream_t s)
+bool launch_split(const bilu_ctx* c, double* F, hipStream_t s)
 {
     const int64_t nP = static_cast<int64_t>(c->h.Pj.size());
     if (c->h.bs > kMaxKernelBs) {
         const int bs = c->h.bs;
         hipLaunchKernelGGL(dev::k_split_gen, dim3(grid_for(nP * bs * bs)), dim3(256), 0, s, nP, bs, c->d_Prow, c->d_Pj,
-                           c->d_P, c->d_Dinv, c->d_F);
+                           c->d_P, c->d_Dinv, F);
         return true;
     }
     BILU_SWITCH_B(c->h.bs, hipLaunchKernelGGL((dev::k_split<B>), dim3(grid_for(nP * B * B)), dim3(256), 0, s, nP,
-                                              c->d_Prow, c->d_Pj, c->d_P, c->d_Dinv, c->d_F))
+                                              c->d_Prow, c->d_Pj, c->d_P, c->d_Dinv, F))
 }
 
 // Sweep layouts with a compile-time block size (k_layout_b, k_layout_dinv_b;
@@ -741,7 +741,7 @@ bilu_status ensure_device(bilu_ctx* c)
             (st = upload(c, &c->d_ATsrc, h.ATsrc)))
             return st;
     }
-    if ((st = dalloc(c, &c->d_P, h.Pj.size() * bb)) || (st = dalloc(c, &c->d_F, h.Pj.size() * bb)) ||
+    if ((st = dalloc(c, &c->d_P, h.Pj.size() * bb)) ||
         (st = dalloc(c, &c->d_Dinv, static_cast<size_t>(h.nb) * bb)) || (st = dalloc(c, &c->d_bad, 1)) ||
         (st = dalloc(c, &c->d_status, 1)) || (st = dalloc(c, &c->d_done, 1)) ||
         (st = dalloc(c, &c->d_ticket, 1)))
@@ -1334,7 +1334,8 @@ static bilu_status ensure_point(bilu_ctx* c, hipStream_t s)
     if (c->point_gen != c->factor_gen) {
         bilu_ctx* p = c->point;
         if (!c->f_ready) {
-            if (!launch_split(c, s)) return BILU_ERR_ARG;
+            if (!c->d_F && (st = dalloc(c, &c->d_F, c->h.Pj.size() * c->h.bs * c->h.bs))) return st;
+            if (!launch_split(c, c->d_F, s)) return BILU_ERR_ARG;
             c->f_ready = true;
         }
         hipLaunchKernelGGL(dev::k_expand_point, dim3(grid_for(c->point_n)), dim3(256), 0, s, c->point_n,
@@ -1599,11 +1600,8 @@ bilu_status bilu_get_info(const bilu_ctx* c, bilu_info* info)
     info->k = h.k;
     info->nnzb_A = static_cast<int64_t>(h.Aj.size());
     info->nnzb_P = static_cast<int64_t>(h.Pj.size());
-    for (int i = 0; i < h.nb; ++i)
-        for (int32_t e = h.Pp[i]; e < h.Pp[i + 1]; ++e) {
-            if (h.Pj[e] < i) info->nnzb_L++;
-            if (h.Pj[e] > i) info->nnzb_U++;
-        }
+    info->nnzb_L = h.nnz_lower;
+    info->nnzb_U = info->nnzb_P - h.nnz_lower - h.nb;     // (every row has its diagonal entry)
     info->rows_per_chunk = h.rpc;
     info->tile_rows = c->tile_rows;
     info->tile_group = built_group(c);
@@ -1729,11 +1727,13 @@ bilu_status bilu_get_factors(const bilu_ctx* c, double* F, double* Dinv, hipStre
     if (!c) return BILU_ERR_ARG;
     if (!c->split_done) return BILU_ERR_STATE;
     const size_t bb = static_cast<size_t>(c->h.bs) * c->h.bs;
-    if (F && !c->f_ready) {
-        if (!launch_split(c, s)) return BILU_ERR_ARG;
-        c->f_ready = true;
+    // formed in the caller's array (the copy of the point view, where there is one)
+    if (F && c->f_ready) {
+        CK(hipMemcpyAsync(F, c->d_F, c->h.Pj.size() * bb * sizeof(double), hipMemcpyDeviceToDevice, s));
+    } else if (F) {
+        if (!launch_split(c, F, s)) return BILU_ERR_ARG;
+        CK(hipGetLastError());
     }
-    if (F) CK(hipMemcpyAsync(F, c->d_F, c->h.Pj.size() * bb * sizeof(double), hipMemcpyDeviceToDevice, s));
     if (Dinv)
         CK(hipMemcpyAsync(Dinv, c->d_Dinv, static_cast<size_t>(c->h.nb) * bb * sizeof(double),
                           hipMemcpyDeviceToDevice, s));

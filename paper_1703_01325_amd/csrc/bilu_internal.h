@@ -268,6 +268,7 @@ struct Host {
     std::vector<int32_t> Arow;             // block row of each stored block of A
     std::vector<int32_t> Pp, Pj, Plev;     // ILU(k) pattern
     std::vector<int32_t> Pdiag;            // position of (i,i) in P
+    int64_t nnz_lower = 0;                 // entries of P below the diagonal
     std::vector<int32_t> Prow;             // block row of each entry of P
     std::vector<int64_t> AtoP;             // position in P of each stored block of A
     std::vector<int32_t> Pfill;            // positions of P not stored in A
