@@ -391,9 +391,18 @@ bool launch_factor(int bs, int64_t first, int nrows, int lds, bilu_ctx* c, hipSt
                                              c->d_bad))
     }
     if (bs > kMaxKernelBs) {
-        const size_t glds = (3 * static_cast<size_t>(bs) * bs + bs) * sizeof(double);
-        hipLaunchKernelGGL(dev::k_factor_rows_gen, dim3(nrows), dim3(256), glds, s, bs, rows, nrows, c->d_Pp,
-                           c->d_Pj, c->d_Pdiag, c->d_upd_ptr, c->d_upd_f, c->d_upd_g, c->d_P, c->d_Dinv, c->d_bad);
+        const int bb = bs * bs;
+        const size_t glds = static_cast<size_t>(3 + std::max(1, 256 / bb)) * bb * sizeof(double);
+        const auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(nrows), dim3(256), glds, s, bs, rows, nrows, c->d_Pp, c->d_Pj, c->d_Pdiag,
+                               c->d_upd_ptr, c->d_upd_f, c->d_upd_g, c->d_P, c->d_Dinv, c->d_bad);
+        };
+        switch ((bb + 255) / 256) {
+        case 1: launch(dev::k_factor_rows_gen<1>); break;
+        case 2: launch(dev::k_factor_rows_gen<2>); break;
+        case 3: launch(dev::k_factor_rows_gen<3>); break;
+        default: launch(dev::k_factor_rows_gen<4>); break;
+        }
         return true;
     }
     BILU_SWITCH_B(bs, hipLaunchKernelGGL((dev::k_factor_rows<B>), dim3(nrows), dim3(64), 0, s, rows, nrows,

@@ -610,104 +610,218 @@ __global__ void k_block_dinv(int64_t nb, const double* __restrict__ Dinv, const 
 // Block ILU(0) on P (Algorithm 4) for the block rows of one L level, block
 // size bs: for each pivot entry (i, p) in order, A_ip <- A_ip D_p^{-1}
 // (staged in LDS), then the update pairs of the host-built lists,
-// A_ij <- A_ij - A_ip A_pj, over (pair, element) in parallel (distinct
-// targets); then D_i^{-1} by Gauss-Jordan with partial pivoting on
-// [A_ii | I].  LDS: bs*bs + 2*bs*bs + bs doubles.
+// A_ij <- A_ij - A_ip A_pj; then D_i^{-1} by Gauss-Jordan with partial
+// pivoting on [A_ii | I].
+//
+// A level of a small grid is a few dozen rows, one workgroup each, so a row's
+// latency is all that counts.  A thread has E elements of a block (1 to 4: bs
+// up to 16, 22, 27 and 32).  The operands of a product come to LDS together,
+// the next pivot's inverse a step ahead and, for E > 1, its first update block
+// with it; for E = 1 as many update pairs run at once as there are threads.
+// [A | I] is held in registers, lane = column, rows dealt over the four
+// wavefronts, and a column's step exchanges its pivot column and the two rows
+// that swap through LDS, two barriers a step (six, with one thread searching
+// the pivot, when the matrix was in LDS).  12^3, bs = 25, ILU(0): 114 us a
+// level before, 44 us so; 9x8x7, bs = 21, ILU(1): 6746 -> 2558 us in all.
+
+// Loads and stores a thread's E elements of a block.
+template <int E>
+__device__ __forceinline__ void gen_load(double (&v)[E], const double* src, int bb)
+{
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+        const int el = static_cast<int>(threadIdx.x) + 256 * m;
+        v[m] = src && el < bb ? src[el] : 0.0;
+    }
+}
+
+template <int E>
+__device__ __forceinline__ void gen_store(double* dst, const double (&v)[E], int bb)
+{
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+        const int el = static_cast<int>(threadIdx.x) + 256 * m;
+        if (el < bb) dst[el] = v[m];
+    }
+}
+
+// A thread's elements of X Y, blocks in LDS, column-major.
+template <int E>
+__device__ __forceinline__ void gen_product(double (&v)[E], const double* X, const double* Y, int bs, int bb)
+{
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+        const int el = static_cast<int>(threadIdx.x) + 256 * m;
+        v[m] = 0.0;
+        if (el < bb) {
+            const int c = el / bs, r = el - c * bs;
+            double acc = 0.0;
+#pragma unroll 8
+            for (int u = 0; u < bs; ++u) acc += X[u * bs + r] * Y[c * bs + u];
+            v[m] = acc;
+        }
+    }
+}
+
+template <int E>
 __global__ __launch_bounds__(256) void k_factor_rows_gen(int bs, const int32_t* __restrict__ rows, int nrows,
                                                          const int32_t* __restrict__ Pp,
                                                          const int32_t* __restrict__ Pj,
                                                          const int32_t* __restrict__ Pdiag,
                                                          const int32_t* __restrict__ upd_ptr,
                                                          const int32_t* __restrict__ upd_f,
-                                                         const int32_t* __restrict__ upd_g, double* __restrict__ P,
-                                                         double* __restrict__ Dinv, int* bad_row)
+                                                         const int32_t* __restrict__ upd_g, double* P, double* Dinv,
+                                                         int* bad_row)
 {
-    extern __shared__ double gsm[];
-    __shared__ int sPiv;
-    __shared__ int sBad;
+    extern __shared__ double gsm[];          // 3 blocks and, for E = 1, as many as have a thread an element
+    __shared__ double sCol[2][32], sPivRow[2][64], sOldRow[2][64];
     if (static_cast<int>(blockIdx.x) >= nrows) return;
     const int bb = bs * bs;
-    const int w2 = 2 * bs;
-    double* sT = gsm;
-    double* sW = gsm + bb;
-    double* sF = sW + 2 * bb;
+    double* sA = gsm;
+    double* sD = sA + bb;
+    double* sT = sD + bb;
+    double* sU = sT + bb;
     const int i = rows[blockIdx.x];
     const int e0 = Pp[i];
     const int d = Pdiag[i];
-    const int t = threadIdx.x;
-    const int nt = blockDim.x;
-    if (t == 0) sBad = 0;
+    double vd[E], vu[E];     // the next D_p^{-1} and A_pj
+    auto ahead = [&](int e) {
+        const bool any = E > 1 && e < d && upd_ptr[e] < upd_ptr[e + 1];
+        gen_load<E>(vd, e < d ? Dinv + static_cast<int64_t>(Pj[e]) * bb : nullptr, bb);
+        if constexpr (E > 1) gen_load<E>(vu, any ? P + static_cast<int64_t>(upd_g[upd_ptr[e]]) * bb : nullptr, bb);
+    };
+    ahead(e0);
     for (int e = e0; e < d; ++e) {
-        const int p = Pj[e];
-        const double* Aip = P + static_cast<int64_t>(e) * bb;
-        const double* Dp = Dinv + static_cast<int64_t>(p) * bb;
-        for (int el = t; el < bb; el += nt) {
-            const int c = el / bs, r = el - (el / bs) * bs;
-            double v = 0.0;
-            for (int u = 0; u < bs; ++u) v += Aip[u * bs + r] * Dp[c * bs + u];
-            sT[el] = v;
-        }
+        double va[E], v[E];
+        // (updates of the step before: by the threads that load here, or behind the barrier)
+        gen_load<E>(va, P + static_cast<int64_t>(e) * bb, bb);
+        const int q0 = upd_ptr[e], q1 = upd_ptr[e + 1];
+        gen_store<E>(sA, va, bb);
+        gen_store<E>(sD, vd, bb);
+        if constexpr (E > 1) gen_store<E>(sU, vu, bb);
         __syncthreads();
-        for (int el = t; el < bb; el += nt) P[static_cast<int64_t>(e) * bb + el] = sT[el];
-        const int q0 = upd_ptr[e];
-        const int64_t work = static_cast<int64_t>(upd_ptr[e + 1] - q0) * bb;
-        for (int64_t x = t; x < work; x += nt) {
-            const int q = q0 + static_cast<int>(x / bb);
-            const int el = static_cast<int>(x % bb);
-            const int c = el / bs, r = el - (el / bs) * bs;
-            const double* Apj = P + static_cast<int64_t>(upd_g[q]) * bb;
-            double acc = 0.0;
-            for (int u = 0; u < bs; ++u) acc += sT[u * bs + r] * Apj[c * bs + u];
-            P[static_cast<int64_t>(e0 + upd_f[q]) * bb + el] -= acc;
-        }
-        __syncthreads();
-    }
-    // Gauss-Jordan on [A_ii | I], row-major in LDS
-    for (int x = t; x < bs * w2; x += nt) {
-        const int r = x / w2, c = x - (x / w2) * w2;
-        sW[x] = c < bs ? P[static_cast<int64_t>(d) * bb + c * bs + r] : (c - bs == r ? 1.0 : 0.0);
-    }
-    __syncthreads();
-    for (int col = 0; col < bs; ++col) {
-        if (t == 0) {
-            int piv = col;
-            double best = fabs(sW[col * w2 + col]);
-            for (int rr = col + 1; rr < bs; ++rr) {
-                const double v = fabs(sW[rr * w2 + col]);
-                if (v > best) {
-                    best = v;
-                    piv = rr;
+        ahead(e + 1);
+        gen_product<E>(v, sA, sD, bs, bb);
+        gen_store<E>(sT, v, bb);
+        gen_store<E>(P + static_cast<int64_t>(e) * bb, v, bb);
+        if constexpr (E == 1) {
+            // as many pairs at once as blocks have threads (their targets differ)
+            const int at_once = 256 / bb;
+            const int g = static_cast<int>(threadIdx.x) / bb, el = static_cast<int>(threadIdx.x) - g * bb;
+            const int c = el / bs, r = el - c * bs;
+            for (int qb = q0; qb < q1; qb += at_once) {
+                const int q = qb + g;
+                const bool on = g < at_once && q < q1;
+                double* target = P + static_cast<int64_t>(e0 + (on ? upd_f[q] : 0)) * bb + el;
+                const double t = on ? *target : 0.0;
+                const double u = on ? P[static_cast<int64_t>(upd_g[q]) * bb + el] : 0.0;
+                __syncthreads();
+                if (on) sU[g * bb + el] = u;
+                __syncthreads();
+                if (on) {
+                    double acc = 0.0;
+#pragma unroll 8
+                    for (int x = 0; x < bs; ++x) acc += sT[x * bs + r] * sU[g * bb + c * bs + x];
+                    *target = t - acc;
                 }
             }
-            if (!(best > 0.0) || !isfinite(best)) sBad = 1;
-            sPiv = piv;
-        }
-        __syncthreads();
-        const int piv = sPiv;
-        if (piv != col)
-            for (int x = t; x < w2; x += nt) {
-                const double tmp = sW[col * w2 + x];
-                sW[col * w2 + x] = sW[piv * w2 + x];
-                sW[piv * w2 + x] = tmp;
+        } else {
+            for (int q = q0; q < q1; ++q) {
+                double* target = P + static_cast<int64_t>(e0 + upd_f[q]) * bb;
+                double t[E];
+                gen_load<E>(t, target, bb);
+                if (q > q0) {
+                    double w[E];
+                    gen_load<E>(w, P + static_cast<int64_t>(upd_g[q]) * bb, bb);
+                    __syncthreads();
+                    gen_store<E>(sU, w, bb);
+                }
+                __syncthreads();
+                gen_product<E>(v, sT, sU, bs, bb);
+#pragma unroll
+                for (int m = 0; m < E; ++m) t[m] -= v[m];
+                gen_store<E>(target, t, bb);
             }
-        __syncthreads();
-        const double dd = sW[col * w2 + col];
-        __syncthreads();
-        for (int x = t; x < w2; x += nt) sW[col * w2 + x] /= dd;
-        __syncthreads();
-        for (int rr = t; rr < bs; rr += nt) sF[rr] = sW[rr * w2 + col];
-        __syncthreads();
-        for (int x = t; x < bs * w2; x += nt) {
-            const int rr = x / w2, cc = x - (x / w2) * w2;
-            if (rr != col) sW[x] -= sF[rr] * sW[col * w2 + cc];
         }
         __syncthreads();
     }
-    for (int el = t; el < bb; el += nt) {
-        const int c = el / bs, r = el - (el / bs) * bs;
-        Dinv[static_cast<int64_t>(i) * bb + el] = sW[r * w2 + bs + c];
+    // Gauss-Jordan on [A_ii | I]: thread (wave, lane) holds rows wave + 4 m of
+    // column lane
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+    const int wave = static_cast<int>(threadIdx.x) >> 6;
+    {
+        double va[E];
+        gen_load<E>(va, P + static_cast<int64_t>(d) * bb, bb);
+        gen_store<E>(sA, va, bb);
     }
-    if (t == 0 && sBad) atomicMin(bad_row, i);
+    __syncthreads();
+    double w[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        const int rr = wave + 4 * m;
+        w[m] = rr >= bs ? 0.0 : lane < bs ? sA[lane * bs + rr] : lane - bs == rr ? 1.0 : 0.0;
+    }
+    bool bad = false;
+    for (int col = 0; col < bs; ++col) {
+        const int h = col & 1;
+        if (lane == col) {
+#pragma unroll
+            for (int m = 0; m < 8; ++m) sCol[h][wave + 4 * m] = w[m];
+        }
+        __syncthreads();
+        // the first of the largest |element| at or below the diagonal, by every
+        // wavefront for itself (a NaN is never larger, and wins where it comes
+        // first)
+        const int mine = lane & 31;
+        const double x = sCol[h][mine];
+        double best = mine >= col && mine < bs ? fabs(x) : -1.0;
+        const bool nan0 = isnan(sCol[h][col]);
+        int piv = mine;
+        if (isnan(best)) best = -1.0;
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) {
+            const double ob = __shfl_xor(best, o);
+            const int op = __shfl_xor(piv, o);
+            if (ob > best || (ob == best && op < piv)) {
+                best = ob;
+                piv = op;
+            }
+        }
+        if (nan0) piv = col;
+        piv = __builtin_amdgcn_readfirstlane(piv);
+        const double dd = sCol[h][piv];
+        bad |= !(fabs(dd) > 0.0) || !isfinite(dd);
+        if (wave == (piv & 3)) {
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+                if (m == piv >> 2) sPivRow[h][lane] = w[m];
+        }
+        if (wave == (col & 3)) {
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+                if (m == col >> 2) sOldRow[h][lane] = w[m];
+        }
+        __syncthreads();
+        const double p = sPivRow[h][lane] / dd;
+        const double old = sOldRow[h][lane];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int rr = wave + 4 * m;
+            const double f = sCol[h][rr == piv ? col : rr];
+            const double base = rr == piv ? old : w[m];
+            w[m] = rr == col ? p : base - f * p;
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        const int rr = wave + 4 * m;
+        if (rr < bs && lane >= bs && lane < 2 * bs) sT[(lane - bs) * bs + rr] = w[m];
+    }
+    __syncthreads();
+    double inv[E];
+    gen_load<E>(inv, sT, bb);
+    gen_store<E>(Dinv + static_cast<int64_t>(i) * bb, inv, bb);
+    if (threadIdx.x == 0 && bad) atomicMin(bad_row, i);
 }
 
 // F from P and D^{-1} (as k_split), block size bs at run time
