@@ -85,7 +85,7 @@ struct bilu_ctx {
     bool dev_ready = false;
     bool factored = false;
     bool split_done = false;
-    bool f_ready = false; // d_F (allocated for the point view) holds the split factors of the current factorisation
+    bool f_ready = false; // d_F (allocated for the point view and for block sizes above kMaxKernelBs) holds the split factors of the current factorisation
     int precision = BILU_FACTORS_FP64;
     int sweep_mode = 2;
     int tile_rows = 0;          // rows per tile of the tiled layouts (0: not chosen yet)
@@ -115,6 +115,7 @@ struct bilu_ctx {
     int32_t *d_Ap = nullptr, *d_Aj = nullptr, *d_Arow = nullptr;
     int32_t *d_Pp = nullptr, *d_Pj = nullptr, *d_Prow = nullptr, *d_Pdiag = nullptr, *d_PtoA = nullptr;
     int32_t* d_Lrows = nullptr;
+    int32_t* d_Urows = nullptr;           // block rows by U' levels (block sizes above kMaxKernelBs)
     // factorisation with rows in LDS: update lists and per L level the LDS
     // bytes of its largest row (0: that level takes k_factor_rows)
     int32_t *d_upd_ptr = nullptr, *d_upd_f = nullptr, *d_upd_g = nullptr;
@@ -126,6 +127,7 @@ struct bilu_ctx {
     // LDS bytes per wavefront (0: some row does not fit, one launch per
     // level instead), ticket and expired-wait words
     int fwave_lds = 0;
+    int gen_blocks = 0;                   // most blocks of a row of L or U' (block sizes above kMaxKernelBs)
     int fwave_n = 16;                     // wavefronts (rows) per workgroup and ticket
     unsigned int* d_fticket = nullptr;
     int factor_mode = 0;                  // BILU_TUNE_FACTOR
@@ -1311,6 +1313,18 @@ static void expand_point_pattern(const Host& h, std::vector<int32_t>& Ap, std::v
         }
 }
 
+// F of the current factors in the context's own array.
+static bilu_status ensure_split(bilu_ctx* c, hipStream_t s)
+{
+    bilu_status st;
+    if (c->f_ready) return BILU_OK;
+    if (!c->d_F && (st = dalloc(c, &c->d_F, c->h.Pj.size() * c->h.bs * c->h.bs))) return st;
+    if (!launch_split(c, c->d_F, s)) return BILU_ERR_ARG;
+    CK(hipGetLastError());
+    c->f_ready = true;
+    return BILU_OK;
+}
+
 // The point view of the current factors: its context (analysed once), then
 // values expanded from F after every factorisation.
 static bilu_status ensure_point(bilu_ctx* c, hipStream_t s)
@@ -1342,11 +1356,7 @@ static bilu_status ensure_point(bilu_ctx* c, hipStream_t s)
     }
     if (c->point_gen != c->factor_gen) {
         bilu_ctx* p = c->point;
-        if (!c->f_ready) {
-            if (!c->d_F && (st = dalloc(c, &c->d_F, c->h.Pj.size() * c->h.bs * c->h.bs))) return st;
-            if (!launch_split(c, c->d_F, s)) return BILU_ERR_ARG;
-            c->f_ready = true;
-        }
+        if ((st = ensure_split(c, s))) return st;
         hipLaunchKernelGGL(dev::k_expand_point, dim3(grid_for(c->point_n)), dim3(256), 0, s, c->point_n,
                            c->d_point_src, c->d_F, p->d_P);
         hipLaunchKernelGGL(dev::k_fill_f64, dim3(grid_for(n)), dim3(256), 0, s, n, p->d_Dinv, 1.0);
@@ -1406,6 +1416,67 @@ static bilu_status do_apply_point(bilu_ctx* c, const double* r, double* z, hipSt
     return run_sweep(p, BILU_SWEEP_U, c->d_point_y, z, p->d_y, 1, s, gate);
 }
 
+// One sweep of a block size above kMaxKernelBs by block rows.
+static bilu_status run_sweep_gen(bilu_ctx* c, int which, const double* rhs, double* out, double* reset, hipStream_t s,
+                                 const int* gate)
+{
+    const Host& h = c->h;
+    const int64_t bb8 = static_cast<int64_t>(h.bs) * h.bs * 8;
+    const long tslot = timing_begin(c, BILU_K_SWEEP_L + which, s);
+    dev::GenSweepArgs a{};
+    const bool upper = which == BILU_SWEEP_U;
+    a.rows = upper ? c->d_Urows : c->d_Lrows;
+    a.Pp = c->d_Pp;
+    a.Pj = c->d_Pj;
+    a.Pdiag = c->d_Pdiag;
+    a.vals = upper ? c->d_F : c->d_P;      // (L is the same in both)
+    a.Dinv = c->d_Dinv;
+    a.rhs = rhs;
+    a.out = out;
+    a.reset = reset;
+    a.ticket = c->d_ticket;
+    a.done = c->d_done;
+    a.status = c->d_status;
+    a.gate = gate;
+    a.bs = h.bs;
+    a.nrows = h.nb;
+    // blocks staged: a row's, as far as four workgroups a compute unit fit
+    // (32 KiB each; the blocks past them come after the first have been used)
+    a.stage = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(c->gen_blocks, 32768 / bb8)));
+    const size_t lds = static_cast<size_t>(a.stage) * (bb8 + 8 * h.bs);
+    // wavefronts for the rows of six levels, one to four a compute unit: enough
+    // to have blocks staged before their turn, few enough not to hinder the
+    // others' polls (one application, us, with 1, 2, 4 and 8 a compute unit:
+    // 12^3 b = 25, 51 rows a level, 165, 173, 186, 203; 24^3 b = 25, 197 rows a
+    // level, 939, 574, 503, 531)
+    const int64_t ahead = 6LL * h.nb / std::max(1, h.sweep[which].nlev);
+    const int per_cu = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(4, ahead / std::max(1, c->num_cu))));
+    const int blocks = persistent_blocks(c, h.nb, 1, per_cu);
+    a.total_waves = static_cast<unsigned int>(blocks);
+    a.spin_limit = c->spin_limit;
+    if (upper) hipLaunchKernelGGL(dev::k_sweep_rows_gen<true>, dim3(blocks), dim3(64), lds, s, a);
+    else hipLaunchKernelGGL(dev::k_sweep_rows_gen<false>, dim3(blocks), dim3(64), lds, s, a);
+    timing_end(c, tslot, s);
+    CK(hipGetLastError());
+    return BILU_OK;
+}
+
+// z = M^{-1} r for block sizes above kMaxKernelBs (one right-hand side): the
+// point rows' products in their order (do_apply_point gives the same bits).
+static bilu_status do_apply_gen(bilu_ctx* c, const double* r, double* z, hipStream_t s, const int* gate)
+{
+    bilu_status st;
+    const Host& h = c->h;
+    if (!c->d_Urows) {
+        for (int32_t i = 0; i < h.nb; ++i)
+            c->gen_blocks = std::max({c->gen_blocks, h.Pdiag[i] - h.Pp[i], h.Pp[i + 1] - h.Pdiag[i] - 1});
+        if ((st = upload(c, &c->d_Urows, h.sweep[BILU_SWEEP_U].level_rows))) return st;
+    }
+    if ((st = ensure_split(c, s)) || (st = ensure_y(c, 1, s))) return st;
+    if ((st = run_sweep_gen(c, BILU_SWEEP_L, r, c->d_y, z, s, gate))) return st;
+    return run_sweep_gen(c, BILU_SWEEP_U, c->d_y, z, c->d_y, s, gate);
+}
+
 // z = M^{-1} r: first sweep r -> y (resets z), second y -> z (resets y).
 bilu_status do_apply(bilu_ctx* c, const double* r, double* z, int R, bool transpose, hipStream_t s,
                      const int* gate = nullptr)
@@ -1413,9 +1484,8 @@ bilu_status do_apply(bilu_ctx* c, const double* r, double* z, int R, bool transp
     if (!c || !r || !z || R < 1 || R > dev::kMaxRhs || r == z) return BILU_ERR_ARG;
     if (!c->split_done) return BILU_ERR_STATE;
     if (c->h.bs > kMaxKernelBs) {
-        // block sizes without block-row sweep kernels: point granularity
         if (R != 1 || transpose) return BILU_ERR_ARG;
-        return do_apply_point(c, r, z, s, gate);
+        return do_apply_gen(c, r, z, s, gate);
     }
     const int first = transpose ? BILU_SWEEP_UT : BILU_SWEEP_L;
     const int second = transpose ? BILU_SWEEP_LT : BILU_SWEEP_U;
@@ -1696,8 +1766,7 @@ bilu_status bilu_factor_diag(bilu_ctx* c, int precision, hipStream_t s)
     if (!c || (precision != BILU_FACTORS_FP64 && precision != BILU_FACTORS_FP32)) return BILU_ERR_ARG;
     if (!c->factored) return BILU_ERR_STATE;
     if (c->h.bs > kMaxKernelBs) {
-        // no block-row sweep layouts: the point view is formed from F when an
-        // application first needs it
+        // no sweep layouts: F is formed when an application first needs it
         if (precision != BILU_FACTORS_FP64) return BILU_ERR_ARG;
         c->f_ready = false;
         c->precision = precision;
