@@ -2375,7 +2375,7 @@ static bilu_status gmres(bilu_ctx* c, const double* Ax, const double* b, double*
     hipLaunchKernelGGL(dev::k_fill_f64, dim3(eg), dim3(256), 0, s, n, x, 0.0);
     hipLaunchKernelGGL(dev::k_fill_i32, dim3(1), dim3(64), 0, s, int64_t(dev::GM_NFLAGS), gv.flags, 0);
     hipLaunchKernelGGL(dev::k_dot, rb, rt, 0, s, n, 1, b, b, part, dev::SL_BB, nullptr);
-    hipLaunchKernelGGL(dev::k_gm_h, dim3(1), dim3(64), 0, s, part, dev::SL_BB, dH, coef, 1, nullptr);
+    hipLaunchKernelGGL(dev::k_gm_h, dim3(1), dim3(64), 0, s, part, dev::SL_BB, dH, coef);
     if ((st = fetch_cycle())) return st;
     const double bnorm = hc->beta;
     const double tol = tol_abs_factor * bnorm;
@@ -2385,7 +2385,7 @@ static bilu_status gmres(bilu_ctx* c, const double* Ax, const double* b, double*
     while (status == BILU_NOT_CONVERGED) {
         if ((st = do_spmv(c, Ax, x, w, 1, tr, s))) break;
         hipLaunchKernelGGL(dev::k_resid, rb, rt, 0, s, n, 1, b, w, part, dev::SL_TRUE, nullptr);
-        hipLaunchKernelGGL(dev::k_gm_h, dim3(1), dim3(64), 0, s, part, dev::SL_TRUE, dH, coef, 1, nullptr);
+        hipLaunchKernelGGL(dev::k_gm_h, dim3(1), dim3(64), 0, s, part, dev::SL_TRUE, dH, coef);
         if ((st = fetch_cycle())) break;
         const double beta = hc->beta;
         if (cycles > 0) total += hc->flags[dev::GM_STEPS];
@@ -2401,18 +2401,19 @@ static bilu_status gmres(bilu_ctx* c, const double* Ax, const double* b, double*
             double* vj = V + static_cast<size_t>(j) * n;
             double* hcol = dH + static_cast<size_t>(j) * (m + 1);
             if ((st = do_apply_spmv(c, Ax, vj, z, w, 1, tr != 0, s, g_active))) break;
-            hipLaunchKernelGGL(dev::k_gm_mgs, rb, rt, 0, s, n, w, nullptr, coef, V, part, dev::SL_RHO, g_active);
-            hipLaunchKernelGGL(dev::k_gm_h, dim3(1), dim3(64), 0, s, part, dev::SL_RHO, hcol, coef, 0, g_active);
-            for (int i = 1; i <= j; ++i) {
-                hipLaunchKernelGGL(dev::k_gm_mgs, rb, rt, 0, s, n, w, V + static_cast<size_t>(i - 1) * n, coef,
-                                   V + static_cast<size_t>(i) * n, part, dev::SL_RHO, g_active);
-                hipLaunchKernelGGL(dev::k_gm_h, dim3(1), dim3(64), 0, s, part, dev::SL_RHO, hcol + i, coef, 0,
-                                   g_active);
-            }
-            hipLaunchKernelGGL(dev::k_gm_mgs, rb, rt, 0, s, n, w, vj, coef, nullptr, part, dev::SL_RHO, g_active);
-            hipLaunchKernelGGL(dev::k_gm_h, dim3(1), dim3(64), 0, s, part, dev::SL_RHO, hcol + j + 1, coef, 1,
+            // the partials of pass i are summed by the pass after it
+            int slot = dev::SL_RHO, other = dev::SL_RV;
+            hipLaunchKernelGGL((dev::k_gm_mgs<false, true>), rb, rt, 0, s, n, w, nullptr, V, part, other, nullptr, slot,
                                g_active);
-            hipLaunchKernelGGL(dev::k_gm_scale, dim3(eg), dim3(256), 0, s, n, w, coef, vj + n, g_active);
+            for (int i = 1; i <= j; ++i) {
+                std::swap(slot, other);
+                hipLaunchKernelGGL((dev::k_gm_mgs<true, true>), rb, rt, 0, s, n, w, V + static_cast<size_t>(i - 1) * n,
+                                   V + static_cast<size_t>(i) * n, part, other, hcol + i - 1, slot, g_active);
+            }
+            std::swap(slot, other);
+            hipLaunchKernelGGL((dev::k_gm_mgs<true, false>), rb, rt, 0, s, n, w, vj, nullptr, part, other, hcol + j, slot,
+                               g_active);
+            hipLaunchKernelGGL(dev::k_gm_normalise, rb, rt, 0, s, n, w, part, slot, hcol + j + 1, vj + n, g_active);
             hipLaunchKernelGGL(dev::k_gm_givens, dim3(1), dim3(64), 0, s, gv, j, steps, tol, c->d_flags + (j & 1));
             if (hipGetLastError() != hipSuccess) { st = BILU_ERR_HIP; break; }
             if (hipEventRecord(c->step_ev[j & 1], s) != hipSuccess) { st = BILU_ERR_HIP; break; }
