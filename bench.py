@@ -26,7 +26,7 @@ sys.path.insert(0, ROOT)
 METRIC = "ILU(k) apply+SpMV HBM GB/s & solves/s to 1e-8 res; FP64 vs FP32-factor vs multi-RHS"
 HBM_PEAK_GBPS = 8000.0
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1703_01325_amd", "csrc", f)
-               for f in ("kernels.h", "sweep_kernels.h", "kernels_batch.h")]
+               for f in ("kernels.h", "sweep_kernels.h", "pencil_kernels.h", "kernels_batch.h")]
 
 
 def kernels_hash():

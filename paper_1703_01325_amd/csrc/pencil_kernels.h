@@ -35,8 +35,8 @@ namespace dev {
 // kept to the instructions it cannot do without: about 0.15 us a level inside
 // a tile at b = 3, ILU(0), and about 1 us more from tile to tile.  Against the
 // row tiles (k_sweep_grouped, k_sweep_tiled, the faster of both), one
-// application on MI355X: 60x220x85, b = 3, ILU(0) 975 -> 488 us, ILU(1) with
-// FP32 factors 2374 -> 794 us; 10^3 ILU(1) 134 -> 47 us; 64^3 ILU(1), 32
+// application on MI355X: 60x220x85, b = 3, ILU(0) 975 -> 469 us, ILU(1) with
+// FP32 factors 2374 -> 781 us; 10^3 ILU(1) 134 -> 47 us; 64^3 ILU(1), 32
 // columns, 4147 -> 1487 us; 120^3 Poisson in blocks of 4, ILU(2), 9109 -> 1780.
 //
 // Rows that other tiles read (and only those) are published in a compact

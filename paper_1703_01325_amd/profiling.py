@@ -81,7 +81,7 @@ def write_traffic(fetch_db, write_db, cfetch_db, cwrite_db, substring, alg_bytes
     write = w_kib * 1024.0 * sw
     here = os.path.dirname(os.path.abspath(__file__))
     hsh = hashlib.sha256()
-    for name in ("kernels.h", "sweep_kernels.h", "kernels_batch.h"):     # as bench.kernels_hash
+    for name in ("kernels.h", "sweep_kernels.h", "pencil_kernels.h", "kernels_batch.h"):     # as bench.kernels_hash
         with open(os.path.join(here, "csrc", name), "rb") as fh:
             hsh.update(fh.read())
     sha = hsh.hexdigest()[:16]
