@@ -51,11 +51,12 @@ constexpr int kMaxTileDoubles = 8192;   // LDS of one tiled wavefront: 64 KiB
 // Scratch of bilu_apply_noalloc, one copy per device for the life of the
 // process: bytes [0, 8) ticket, [8, 12) done count and [12, 16) status of the
 // persistent sweeps, from byte kScratchHeader the intermediate vector y of
-// the application.  Host code uses the address hipGetSymbolAddress gives for
-// the current device, never the symbol itself.
-constexpr size_t kScratchBytes = size_t(32) << 20;
+// the application, from byte kScratchVector the exchange arrays of its two
+// pencil sweeps (each at most as long as y).  Host code uses the address
+// hipGetSymbolAddress gives for the current device, never the symbol itself.
 constexpr size_t kScratchHeader = 256;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kScratchVector = size_t(32) << 20;
+static __device__ __align__(256) unsigned char scratch[3 * kScratchVector];
 
 namespace {
 constexpr int kScratchDevices = 64;
@@ -948,14 +949,6 @@ bilu_status layout_pencil(bilu_ctx* c, bool transpose, hipStream_t s)
 }
 
 // Work space of an application by pencil sweeps of R columns.
-bool pencil_work_fits(const bilu_ctx* c, bool transpose, int R)
-{
-    if (c->pw_cap < static_cast<size_t>(c->h.nb) * c->h.bs * R) return false;
-    for (int w : {transpose ? BILU_SWEEP_UT : BILU_SWEEP_L, transpose ? BILU_SWEEP_LT : BILU_SWEEP_U})
-        if (c->pencil[w].exch_cap < static_cast<size_t>(c->h.pencil[w].nexch) * c->h.bs * R) return false;
-    return true;
-}
-
 bilu_status ensure_pencil_work(bilu_ctx* c, bool transpose, int R, hipStream_t s)
 {
     bilu_status st;
@@ -983,16 +976,30 @@ bilu_status ensure_pencil_work(bilu_ctx* c, bool transpose, int R, hipStream_t s
     return BILU_OK;
 }
 
-// One pencil sweep of ncol columns of rhs (rows of rhs_R columns) into out
-// (rows of out_R columns); fuse: the second sweep of the pair, whose right-hand
-// side is D^{-1} (its transpose for the transposed pair) times rhs.
-bilu_status run_pencil(bilu_ctx* c, int which, int other, const double* rhs, int rhs_R, double* out, int out_R,
-                       int ncol, bool fuse, hipStream_t s, const int* gate, bool timed)
+// Ticket, done count and status of a persistent sweep launch.
+struct SweepSync {
+    unsigned long long* ticket;
+    unsigned int* done;
+    int* status;
+};
+
+// What a pair of pencil sweeps works in: the vector between them, the exchange
+// array of every sweep (kNotReady before the pair) and the counters.
+struct PencilWork {
+    double* mid;
+    double* exch[4];
+    SweepSync sync;
+};
+
+// One pencil sweep of R columns; fuse: the second sweep of the pair, whose
+// right-hand side is D^{-1} (its transpose for the transposed pair) times rhs.
+bilu_status run_pencil(bilu_ctx* c, int which, int other, const PencilWork& wk, const double* rhs, double* out, int R,
+                       bool fuse, hipStream_t s, const int* gate, bool timed)
 {
     const long tslot = timed ? timing_begin(c, BILU_K_SWEEP_L + which, s) : -1;
     const HostPencil& hp = c->h.pencil[which];
     const DevPencil& d = c->pencil[which];
-    const int cb = pencil_columns(c, hp, ncol);
+    const int cb = pencil_columns(c, hp, R);
     dev::PencilArgs a{};
     a.tile_ptr = d.tile_ptr;
     a.ext_ptr = d.ext_ptr;
@@ -1002,21 +1009,20 @@ bilu_status run_pencil(bilu_ctx* c, int which, int other, const double* rhs, int
     a.dinv = c->d_Dinv;
     a.rhs = rhs;
     a.out = out;
-    a.exch = d.exch;
-    a.reset = c->pencil[other].exch;
-    a.nreset = c->h.pencil[other].nexch * c->h.bs * ncol;
+    a.exch = wk.exch[which];
+    a.reset = wk.exch[other];
+    a.nreset = c->h.pencil[other].nexch * c->h.bs * R;
     a.nexch = hp.nexch;
-    a.ticket = c->d_ticket;
-    a.done = c->d_done;
-    a.status = c->d_status;
+    a.ticket = wk.sync.ticket;
+    a.done = wk.sync.done;
+    a.status = wk.sync.status;
     a.gate = gate;
     a.ntiles = hp.ntiles;
-    a.ncg = ncol / cb;
+    a.ncg = R / cb;
     a.ring = hp.ring;
     a.reach = hp.reach;
     a.ext_ring = hp.ext_ring;
-    a.rhs_R = rhs_R;
-    a.out_R = out_R;
+    a.rhs_R = a.out_R = R;
     a.transposed = transposed_sweep(which) ? 1 : 0;
     a.spin_limit = c->spin_limit;
     const int blocks = persistent_blocks(c, hp.ntiles * a.ncg, 1, 2);
@@ -1028,15 +1034,23 @@ bilu_status run_pencil(bilu_ctx* c, int which, int other, const double* rhs, int
     return BILU_OK;
 }
 
-// z = M^{-1} r (or M^{-T} r): columns [0, ncol) of r and z, rows of R columns.
-bilu_status pencil_pair(bilu_ctx* c, const double* r, double* z, int R, int ncol, bool transpose, hipStream_t s,
-                        const int* gate, bool timed = true)
+// z = M^{-1} r (or M^{-T} r), R columns.
+bilu_status pencil_pair(bilu_ctx* c, const PencilWork& wk, const double* r, double* z, int R, bool transpose,
+                        hipStream_t s, const int* gate, bool timed)
 {
     const int first = transpose ? BILU_SWEEP_UT : BILU_SWEEP_L;
     const int second = transpose ? BILU_SWEEP_LT : BILU_SWEEP_U;
-    bilu_status st = run_pencil(c, first, second, r, R, c->d_pw, ncol, ncol, false, s, gate, timed);
+    bilu_status st = run_pencil(c, first, second, wk, r, wk.mid, R, false, s, gate, timed);
     if (st) return st;
-    return run_pencil(c, second, first, c->d_pw, ncol, z, R, ncol, true, s, gate, timed);
+    return run_pencil(c, second, first, wk, wk.mid, z, R, true, s, gate, timed);
+}
+
+// The context's own work space (ensure_pencil_work).
+PencilWork pencil_work(const bilu_ctx* c)
+{
+    PencilWork wk{c->d_pw, {}, {c->d_ticket, c->d_done, c->d_status}};
+    for (int w = 0; w < 4; ++w) wk.exch[w] = c->pencil[w].exch;
+    return wk;
 }
 
 // D^{-1} y by blocks ahead of an unfused U' sweep instead of inside it
@@ -1088,13 +1102,6 @@ bilu_status ensure_y(bilu_ctx* c, int R, hipStream_t s)
 long long* g_trace_buf[4] = {nullptr, nullptr, nullptr, nullptr};
 size_t g_trace_n[4] = {0, 0, 0, 0};
 #endif
-
-// Ticket, done count and status of a persistent sweep launch.
-struct SweepSync {
-    unsigned long long* ticket;
-    unsigned int* done;
-    int* status;
-};
 
 // sync: counters to use instead of the context's (may be null); timed:
 // recorded in bilu_timing's sweep classes.
@@ -1493,7 +1500,7 @@ bilu_status do_apply(bilu_ctx* c, const double* r, double* z, int R, bool transp
     bilu_status st;
     if (use_pencil(c, transpose, R)) {
         if ((st = layout_pencil(c, transpose, s)) || (st = ensure_pencil_work(c, transpose, R, s))) return st;
-        return pencil_pair(c, r, z, R, R, transpose, s, gate);
+        return pencil_pair(c, pencil_work(c), r, z, R, transpose, s, gate, true);
     }
     const int form = sweep_form(c, R);
     if ((st = layout_form(c, form, s))) return st;
@@ -1856,28 +1863,17 @@ bilu_status bilu_apply_noalloc(bilu_ctx* c, const double* r, double* z, int nrhs
 {
     if (!c || !r || !z || nrhs < 1 || nrhs > dev::kMaxRhs || r == z || c->h.bs > kMaxKernelBs) return BILU_ERR_ARG;
     const int64_t ny = static_cast<int64_t>(c->h.nb) * c->h.bs * nrhs;
-    if (static_cast<size_t>(ny) * sizeof(double) > kScratchBytes - kScratchHeader) return BILU_ERR_ARG;
+    if (static_cast<size_t>(ny) * sizeof(double) > kScratchVector - kScratchHeader) return BILU_ERR_ARG;
     if (!c->dev_ready || !c->split_done) return BILU_ERR_STATE;
-    if (use_pencil(c, false, nrhs)) {
-        // work space of the context: columns it does not hold together run
-        // one after the other (the factorisation made room for one)
-        int device = -1;
-        CK(hipGetDevice(&device));
-        if (device != c->device) return BILU_ERR_STATE;
-        for (int w : {static_cast<int>(BILU_SWEEP_L), static_cast<int>(BILU_SWEEP_U)})
-            if (c->pencil[w].vals_precision != c->precision) return BILU_ERR_STATE;
-        const int ncol = pencil_work_fits(c, false, nrhs) ? nrhs : 1;
-        if (!pencil_work_fits(c, false, ncol)) return BILU_ERR_STATE;
-        for (int j = 0; j < nrhs; j += ncol) {
-            const bilu_status st = pencil_pair(c, r + j, z + j, nrhs, ncol, false, s, nullptr, false);
-            if (st) return st;
-        }
-        return BILU_OK;
-    }
+    const bool pencil = use_pencil(c, false, nrhs);
     // the layouts of this form must already hold the current factors: laying
     // them out would allocate
     const int form = sweep_form(c, nrhs);
     for (int w : {static_cast<int>(BILU_SWEEP_L), static_cast<int>(BILU_SWEEP_U)}) {
+        if (pencil) {
+            if (c->pencil[w].vals_precision != c->precision) return BILU_ERR_STATE;
+            continue;
+        }
         const int f = use_lines(c, w, nrhs) ? kFormLines : form;
         if (!c->form_uploaded[f] || !c->h.sweep[w].built || c->ds[f][w].vals_precision != c->precision)
             return BILU_ERR_STATE;
@@ -1891,13 +1887,29 @@ bilu_status bilu_apply_noalloc(bilu_ctx* c, const double* r, double* z, int nrhs
     const SweepSync sync{reinterpret_cast<unsigned long long*>(base), reinterpret_cast<unsigned int*>(base + 8),
                          reinterpret_cast<int*>(base + 12)};
     double* y = reinterpret_cast<double*>(base + kScratchHeader);
-    // the scratch keeps the last call's contents: counters cleared and y set
-    // to kNotReady by fill kernels on every call
+    // the scratch keeps the last call's contents: counters cleared and what
+    // the sweeps poll (y, the exchange arrays of pencils) set to kNotReady by
+    // fill kernels on every call.  Nothing here belongs to the context, whose
+    // own work space moves when an application brings more columns: a captured
+    // call stays good, and calls may overlap with the context's other calls.
     hipLaunchKernelGGL(dev::k_fill_i32, dim3(1), dim3(64), 0, s, int64_t(4), reinterpret_cast<int32_t*>(base), 0);
-    hipLaunchKernelGGL(dev::k_fill_not_ready, dim3(grid_for(ny)), dim3(256), 0, s, ny, y);
-    CK(hipGetLastError());
-    if ((st = run_sweep(c, BILU_SWEEP_L, r, y, z, nrhs, s, nullptr, &sync, false))) return st;
-    if ((st = run_sweep(c, BILU_SWEEP_U, y, z, y, nrhs, s, nullptr, &sync, false))) return st;
+    if (pencil) {
+        const int64_t first = c->h.pencil[BILU_SWEEP_L].nexch * c->h.bs * nrhs;
+        const int64_t both = first + c->h.pencil[BILU_SWEEP_U].nexch * c->h.bs * nrhs;
+        if (both > 2 * ny) return BILU_ERR_STATE;
+        double* exch = reinterpret_cast<double*>(base + kScratchVector);
+        PencilWork wk{y, {}, sync};
+        wk.exch[BILU_SWEEP_L] = exch;
+        wk.exch[BILU_SWEEP_U] = exch + first;
+        hipLaunchKernelGGL(dev::k_fill_not_ready, dim3(grid_for(both)), dim3(256), 0, s, both, exch);
+        CK(hipGetLastError());
+        if ((st = pencil_pair(c, wk, r, z, nrhs, false, s, nullptr, false))) return st;
+    } else {
+        hipLaunchKernelGGL(dev::k_fill_not_ready, dim3(grid_for(ny)), dim3(256), 0, s, ny, y);
+        CK(hipGetLastError());
+        if ((st = run_sweep(c, BILU_SWEEP_L, r, y, z, nrhs, s, nullptr, &sync, false))) return st;
+        if ((st = run_sweep(c, BILU_SWEEP_U, y, z, y, nrhs, s, nullptr, &sync, false))) return st;
+    }
     // a bounded wait that expired shows in bilu_check and the solvers, as for
     // bilu_apply
     hipLaunchKernelGGL(dev::k_merge_status, dim3(1), dim3(64), 0, s, sync.status, c->d_status);
