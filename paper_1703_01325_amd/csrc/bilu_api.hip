@@ -872,10 +872,14 @@ bilu_status layout_form(bilu_ctx* c, int form, hipStream_t s)
 // a pencil layout for both: grid lines in natural order and rows no wider than
 // the kernels.  Every pattern measured that has one ran faster that way (2 to
 // 7 times, figures at k_sweep_pencil), so there is no other condition.
+bool row_tiles_asked(const bilu_ctx* c)
+{
+    return c->tile_rows_req != 0 || c->tile_group_req != 0 || c->tile_block != 0 || c->line_block != 0;
+}
+
 bool pencil_wanted(const bilu_ctx* c)
 {
-    return !c->values_only && c->sweep_mode == 2 && c->h.bs <= kMaxKernelBs &&
-           c->tile_rows_req == 0 && c->tile_group_req == 0 && c->tile_block == 0 && c->line_block == 0 &&
+    return !c->values_only && c->sweep_mode == 2 && c->h.bs <= kMaxKernelBs && !row_tiles_asked(c) &&
            c->helper == 0 && c->rhs_pairs == 0 && c->split_dinv == 0 && !c->fuse_spmv && c->blocks_override == 0;
 }
 
@@ -946,6 +950,18 @@ bilu_status layout_pencil(bilu_ctx* c, bool transpose, hipStream_t s)
         d.vals_precision = c->precision;
     }
     return BILU_OK;
+}
+
+// Whether an application of R columns may run on pencil layouts that hold the
+// current factors, without a change on the device.  (Not where a row-tile
+// layout was asked for; the knobs of the row tiles' launches change no layout,
+// so it does not matter whether one was set or cleared since the factorisation.)
+bool pencil_held(const bilu_ctx* c, int R)
+{
+    if (sweep_form(c, R) != kFormTiled || row_tiles_asked(c)) return false;
+    for (int w : {BILU_SWEEP_L, BILU_SWEEP_U})
+        if (!c->h.pencil[w].built || c->pencil[w].vals_precision != c->precision) return false;
+    return true;
 }
 
 // Work space of an application by pencil sweeps of R columns.
@@ -1865,15 +1881,12 @@ bilu_status bilu_apply_noalloc(bilu_ctx* c, const double* r, double* z, int nrhs
     const int64_t ny = static_cast<int64_t>(c->h.nb) * c->h.bs * nrhs;
     if (static_cast<size_t>(ny) * sizeof(double) > kScratchVector - kScratchHeader) return BILU_ERR_ARG;
     if (!c->dev_ready || !c->split_done) return BILU_ERR_STATE;
-    const bool pencil = use_pencil(c, false, nrhs);
-    // the layouts of this form must already hold the current factors: laying
-    // them out would allocate
+    // the layouts must already hold the current factors: laying them out would
+    // allocate
+    const bool pencil = pencil_held(c, nrhs);
     const int form = sweep_form(c, nrhs);
     for (int w : {static_cast<int>(BILU_SWEEP_L), static_cast<int>(BILU_SWEEP_U)}) {
-        if (pencil) {
-            if (c->pencil[w].vals_precision != c->precision) return BILU_ERR_STATE;
-            continue;
-        }
+        if (pencil) break;
         const int f = use_lines(c, w, nrhs) ? kFormLines : form;
         if (!c->form_uploaded[f] || !c->h.sweep[w].built || c->ds[f][w].vals_precision != c->precision)
             return BILU_ERR_STATE;

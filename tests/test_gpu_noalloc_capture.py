@@ -75,3 +75,51 @@ def test_noalloc_beside_apply(api):
         assert torch.equal(z1, want1) and torch.equal(z2, want2)
     M.check()
     M.close()
+
+
+LAUNCH_KNOBS = [dict(helper=True), dict(helper=False), dict(rhs_pairs=True), dict(split_dinv=True),
+                dict(split_dinv=False), dict(fuse_spmv=True), dict(blocks=7)]
+DEFAULTS = dict(helper="auto", rhs_pairs="auto", split_dinv="auto", fuse_spmv=False, blocks=0)
+
+
+@pytest.mark.parametrize("knob", LAUNCH_KNOBS, ids=[f"{k}-{v}" for d in LAUNCH_KNOBS for k, v in d.items()])
+def test_noalloc_after_a_launch_knob(api, knob):
+    """A knob that shapes no layout, set or cleared after the factorisation,
+    does not take the layouts away."""
+    s = synth.reservoir(9, 10, 11, 3, seed=23)
+    Ax = torch.from_numpy(s.Ax).cuda()
+    r = torch.randn(s.n, dtype=torch.float64, device="cuda")
+    P = api.BlockILU(s.nb, s.bs, s.Ap, s.Aj, 1)
+    assert P.factor(Ax) == -1
+    want = P.apply(r)
+    for before, after in (({}, knob), (knob, {k: DEFAULTS[k] for k in knob})):
+        M = api.BlockILU(s.nb, s.bs, s.Ap, s.Aj, 1)
+        M.tune(**before)
+        assert M.factor(Ax) == -1
+        M.tune(**after)
+        z = torch.empty_like(r)
+        _noalloc(M, r, z)
+        assert torch.equal(z, want)
+        M.check()
+        M.close()
+
+
+def test_noalloc_after_another_layout_is_asked_for(api):
+    """A knob that asks for other layouts leaves none that hold the factors
+    (until an application lays them out)."""
+    from paper_1703_01325_amd import _native as N
+    s = synth.reservoir(9, 10, 11, 3, seed=24)
+    r = torch.randn(s.n, dtype=torch.float64, device="cuda")
+    z = torch.empty_like(r)
+    for knob in (dict(tile_rows=17), dict(tile_block=(2, 3)), dict(mode=1)):
+        M = api.BlockILU(s.nb, s.bs, s.Ap, s.Aj, 1)
+        assert M.factor(torch.from_numpy(s.Ax).cuda()) == -1
+        M.tune(**knob)
+        with pytest.raises(N.BiluError) as ei:
+            _noalloc(M, r, z)
+        assert ei.value.code == N.ERR_STATE
+        want = M.apply(r)
+        _noalloc(M, r, z)
+        assert torch.equal(z, want)
+        M.check()
+        M.close()
