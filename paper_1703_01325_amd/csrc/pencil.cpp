@@ -345,6 +345,7 @@ int validate_pencil(const Host& h, const HostPencil& s)
             for (int q = 0; q < rpc; ++q) {
                 const int32_t row = s.rows[static_cast<size_t>(c) * rpc + q];
                 int found = 0;
+                int32_t last = -1;
                 for (int k = 0; k < s.width; ++k) {
                     const uint32_t two = word(c, q, k / 2);
                     const int code = static_cast<int>(k % 2 ? two >> 16 : two & 0xffffu);
@@ -375,7 +376,10 @@ int validate_pencil(const Host& h, const HostPencil& s)
                     const int32_t pi = h.Prow[e], pj = h.Pj[e];
                     if (rowwise ? (pi != row || pj != j) : (pi != j || pj != row)) return BILU_ERR_STATE;
                     if (pi == pj || (pj < pi) != (w == BILU_SWEEP_L || w == BILU_SWEEP_LT)) return BILU_ERR_STATE;
-                    // ascending columns: the order in which every sweep sums
+                    // ascending columns, the order in which every sweep sums (and
+                    // so none twice)
+                    if (j <= last) return BILU_ERR_STATE;
+                    last = j;
                     ++found;
                 }
                 if (row >= 0 && found != ndep[row]) return BILU_ERR_STATE;
