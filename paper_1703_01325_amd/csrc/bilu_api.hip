@@ -883,13 +883,24 @@ bool pencil_wanted(const bilu_ctx* c)
            c->helper == 0 && c->rhs_pairs == 0 && c->split_dinv == 0 && !c->fuse_spmv && c->blocks_override == 0;
 }
 
+// The pencil layout of a sweep, built on first use (not kept if memory runs out
+// on the way).
+const HostPencil& host_pencil(Host& h, int w)
+{
+    if (!h.pencil[w].tried) {
+        HostPencil hp;
+        build_pencil(h, w, h.rpc, hp);
+        h.pencil[w] = std::move(hp);
+    }
+    return h.pencil[w];
+}
+
 bool use_pencil(bilu_ctx* c, bool transpose, int R)
 {
     if (!pencil_wanted(c) || sweep_form(c, R) != kFormTiled) return false;
     for (int w : {transpose ? BILU_SWEEP_UT : BILU_SWEEP_L, transpose ? BILU_SWEEP_LT : BILU_SWEEP_U}) {
         if (!c->h.sweep[w].built) return false;
-        HostPencil& hp = c->h.pencil[w];
-        if (!hp.tried) build_pencil(c->h, w, c->h.rpc, hp);
+        const HostPencil& hp = host_pencil(c->h, w);
         if (!hp.built || pencil_lds(c, hp, 1) > c->lds_max) return false;
     }
     return true;
@@ -1503,7 +1514,7 @@ static bilu_status do_apply_gen(bilu_ctx* c, const double* r, double* z, hipStre
 // z = M^{-1} r: first sweep r -> y (resets z), second y -> z (resets y).
 bilu_status do_apply(bilu_ctx* c, const double* r, double* z, int R, bool transpose, hipStream_t s,
                      const int* gate = nullptr)
-{
+try {
     if (!c || !r || !z || R < 1 || R > dev::kMaxRhs || r == z) return BILU_ERR_ARG;
     if (!c->split_done) return BILU_ERR_STATE;
     if (c->h.bs > kMaxKernelBs) {
@@ -1528,6 +1539,8 @@ bilu_status do_apply(bilu_ctx* c, const double* r, double* z, int R, bool transp
         return run_sweep(c, second, c->d_y, z, c->d_y, R, s, gate, nullptr, true, c->d_y2);
     }
     return run_sweep(c, second, c->d_y, z, c->d_y, R, s, gate);
+} catch (const std::bad_alloc&) {
+    return BILU_ERR_ALLOC;      // (layouts are formed on first use)
 }
 
 // timed: counted in the SpMV class of bilu_timing (the solvers' gated
@@ -1719,7 +1732,7 @@ bilu_status bilu_get_info(const bilu_ctx* c, bilu_info* info)
 }
 
 bilu_status bilu_validate(const bilu_ctx* c)
-{
+try {
     if (!c) return BILU_ERR_ARG;
     // the pencil layouts too, also before the first factorisation builds them
     if (pencil_wanted(c))
@@ -1731,6 +1744,8 @@ bilu_status bilu_validate(const bilu_ctx* c)
             if (use.built && validate_pencil(c->h, use) != BILU_OK) return BILU_ERR_STATE;
         }
     return static_cast<bilu_status>(validate_layout(c->h));
+} catch (const std::bad_alloc&) {
+    return BILU_ERR_ALLOC;
 }
 
 bilu_status bilu_factor_numeric(bilu_ctx* c, const double* Ax, hipStream_t s, int* bad_row)
@@ -1785,7 +1800,7 @@ bilu_status bilu_factor_numeric(bilu_ctx* c, const double* Ax, hipStream_t s, in
 }
 
 bilu_status bilu_factor_diag(bilu_ctx* c, int precision, hipStream_t s)
-{
+try {
     if (!c || (precision != BILU_FACTORS_FP64 && precision != BILU_FACTORS_FP32)) return BILU_ERR_ARG;
     if (!c->factored) return BILU_ERR_STATE;
     if (c->h.bs > kMaxKernelBs) {
@@ -1821,6 +1836,8 @@ bilu_status bilu_factor_diag(bilu_ctx* c, int precision, hipStream_t s)
     c->split_done = true;
     ++c->factor_gen;
     return BILU_OK;
+} catch (const std::bad_alloc&) {
+    return BILU_ERR_ALLOC;
 }
 
 bilu_status bilu_get_factors(const bilu_ctx* c, double* F, double* Dinv, hipStream_t s)
