@@ -46,6 +46,11 @@
 namespace {
 
 constexpr int kHash = 1024;          // hash slots of the largest row search; it may reach 3/4 as many vertices
+// Up to this many rows a search is its launches and allocations: one launch with
+// the largest table (7 points, one launch against small tables and lists: k = 1,
+// 8000 rows 306 and 355 us, 15625 rows 372 and 332; k = 0, 15625 rows 293 and 311,
+// 27000 rows 341 and 310).
+constexpr int few_rows(int k) { return k == 0 ? 24000 : 10000; }
 constexpr unsigned short kKept = 0x8000u;
 constexpr unsigned int kSpinLimit = 1u << 20;
 
@@ -110,6 +115,9 @@ __device__ __forceinline__ int table_slot(RowTable<SLOTS>& t, int v)
             if (atomicAdd(&t.nused, 1) >= SLOTS / 4 * 3) t.over = 1;
             return static_cast<int>(h);
         }
+        // (a table given up is not filled to its last slot: every vertex more
+        // would probe all of it)
+        if (__hip_atomic_load(&t.over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) return -1;
         h = (h + 1) & (SLOTS - 1);
     }
     t.over = 1;
@@ -491,35 +499,52 @@ bilu_status status_to_error(int st)
         if ((call) != hipSuccess) return BILU_ERR_HIP; \
     } while (0)
 
-// Searches all rows: first in tables for what a row of this k reaches on a
-// 7-point grid (19, 43, 86 and 151 vertices for k = 1 to 4; a table takes 3/4
-// of its slots), the rows that outgrow them in larger ones.
+// Searches all rows: first in tables for what a row is expected to reach (a
+// table takes 3/4 of its slots), the rows that outgrow them in larger ones.  On a
+// 7-point grid a row reaches 7, 19, 43, 86 and 151 vertices for k = 0 to 4, 0.7
+// times those within k + 1 steps, on a 27-point grid about 0.65 times the cube of
+// that radius; a pattern is taken for the one or the other by its entries a row,
+// and to spread in proportion to them.  A first guess too low costs the searches
+// up to where the table is given up: 27 points, 30^3, k = 2, in tables of 256
+// slots first 2152 us, in the largest at once 1447 us.
 template <bool WRITE>
-bilu_status search_rows(int nb, const int32_t* Ap, const int32_t* Aj, int k, int32_t* cnt, const int32_t* Pp,
-                        int32_t* Pj, int32_t* Plev, int* d_status, Scratch& sc, hipStream_t s)
+bilu_status search_rows(int nb, int64_t nnz, const int32_t* Ap, const int32_t* Aj, int k, int32_t* cnt,
+                        const int32_t* Pp, int32_t* Pj, int32_t* Plev, int* d_status, Scratch& sc, hipStream_t s)
 {
-    int* over = sc.get<int>(2);                                    // lengths of the two lists
-    int32_t* list1 = sc.get<int32_t>(static_cast<size_t>(nb));
-    int32_t* list2 = sc.get<int32_t>(static_cast<size_t>(nb));
-    if (!over || !list1 || !list2) return BILU_ERR_ALLOC;
+    if (nb <= few_rows(k)) {
+        k_sym_rows<kHash, 64, WRITE><<<nb, 64, 0, s>>>(nb, nullptr, nullptr, Ap, Aj, k, cnt, Pp, Pj, Plev, nullptr,
+                                                       nullptr, d_status);
+        return BILU_OK;
+    }
+    const double steps = k + 1.0;
+    const double side = 2.0 * steps + 1.0, mean = static_cast<double>(nnz) / nb;
+    const double reach = mean <= 13.0 ? 0.1 * mean * side * (2.0 * steps * steps + 2.0 * steps + 3.0) / 3.0
+                                      : 0.65 * mean * (side / 3.0) * (side / 3.0) * (side / 3.0);
+    int* over = sc.get<int>(2 + 2 * static_cast<size_t>(nb));     // lengths of the two lists, and these
+    if (!over) return BILU_ERR_ALLOC;
+    int32_t* list1 = over + 2;
+    int32_t* list2 = list1 + nb;
     CKH(hipMemsetAsync(over, 0, 2 * sizeof(int), s));
     const auto grid = [nb](int rows) { return std::min((nb + rows - 1) / rows, 65536); };
-    if (k <= 2)
+    if (reach <= 48)
         k_sym_rows<64, 16, WRITE><<<grid(4), 64, 0, s>>>(nb, nullptr, nullptr, Ap, Aj, k, cnt, Pp, Pj, Plev, list1,
                                                          over, d_status);
-    else
+    else if (reach <= 96)
         k_sym_rows<128, 32, WRITE><<<grid(2), 64, 0, s>>>(nb, nullptr, nullptr, Ap, Aj, k, cnt, Pp, Pj, Plev, list1,
                                                           over, d_status);
-    k_sym_rows<256, 64, WRITE><<<std::min(nb, 8192), 64, 0, s>>>(nb, list1, over, Ap, Aj, k, cnt, Pp, Pj, Plev, list2,
-                                                                 over + 1, d_status);
-    k_sym_rows<kHash, 64, WRITE><<<std::min(nb, 2048), 64, 0, s>>>(nb, list2, over + 1, Ap, Aj, k, cnt, Pp, Pj, Plev,
-                                                                   nullptr, nullptr, d_status);
+    const bool all256 = reach > 96 && reach <= 192, all = reach > 192;
+    if (!all)
+        k_sym_rows<256, 64, WRITE><<<std::min(nb, all256 ? 65536 : 8192), 64, 0, s>>>(
+            nb, all256 ? nullptr : list1, over, Ap, Aj, k, cnt, Pp, Pj, Plev, list2, over + 1, d_status);
+    k_sym_rows<kHash, 64, WRITE><<<std::min(nb, all ? 65536 : 2048), 64, 0, s>>>(
+        nb, all ? nullptr : list2, over + 1, Ap, Aj, k, cnt, Pp, Pj, Plev, nullptr, nullptr, d_status);
     return BILU_OK;
 }
 
 // Checks the pattern, sizes the rows and writes the row pointers; *nnzb
-// receives the entry count.
-bilu_status sym_count(int nb, const int32_t* Ap, const int32_t* Aj, int k, int32_t* Pp, int64_t* nnzb, hipStream_t s)
+// receives the entry count, *nnzA that of A.
+bilu_status sym_count(int nb, const int32_t* Ap, const int32_t* Aj, int k, int32_t* Pp, int64_t* nnzb, int32_t* nnzA,
+                      hipStream_t s)
 {
     Scratch sc;
     int* d_status = sc.get<int>(1);
@@ -531,10 +556,12 @@ bilu_status sym_count(int nb, const int32_t* Ap, const int32_t* Aj, int k, int32
     k_check_ptr<<<1, 64, 0, s>>>(nb, Ap, d_status);
     k_check_pattern<<<grid_for(nb, 256), 256, 0, s>>>(nb, Ap, Aj, d_status);
     int h_status = 0;
+    *nnzA = 0;
     CKH(hipMemcpyAsync(&h_status, d_status, sizeof(int), hipMemcpyDeviceToHost, s));
+    if (nb > few_rows(k)) CKH(hipMemcpyAsync(nnzA, Ap + nb, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     CKH(hipStreamSynchronize(s));
     if (h_status) return status_to_error(h_status);
-    const bilu_status st = search_rows<false>(nb, Ap, Aj, k, cnt, nullptr, nullptr, nullptr, d_status, sc, s);
+    const bilu_status st = search_rows<false>(nb, *nnzA, Ap, Aj, k, cnt, nullptr, nullptr, nullptr, d_status, sc, s);
     if (st != BILU_OK) return st;
     size_t tmp_bytes = 0;
     if (rocprim::exclusive_scan(nullptr, tmp_bytes, cnt, ptr64, int64_t(0), static_cast<size_t>(nb) + 1,
@@ -558,14 +585,14 @@ bilu_status sym_count(int nb, const int32_t* Ap, const int32_t* Aj, int k, int32
 }
 
 // Writes the rows at the pointers sym_count produced.
-bilu_status sym_write(int nb, const int32_t* Ap, const int32_t* Aj, int k, const int32_t* Pp, int32_t* Pj,
+bilu_status sym_write(int nb, int32_t nnzA, const int32_t* Ap, const int32_t* Aj, int k, const int32_t* Pp, int32_t* Pj,
                       int32_t* Plev, hipStream_t s)
 {
     Scratch sc;
     int* d_status = sc.get<int>(1);
     if (!d_status) return BILU_ERR_ALLOC;
     CKH(hipMemsetAsync(d_status, 0, sizeof(int), s));
-    const bilu_status st = search_rows<true>(nb, Ap, Aj, k, nullptr, Pp, Pj, Plev, d_status, sc, s);
+    const bilu_status st = search_rows<true>(nb, nnzA, Ap, Aj, k, nullptr, Pp, Pj, Plev, d_status, sc, s);
     if (st != BILU_OK) return st;
     int h_status = 0;
     CKH(hipMemcpyAsync(&h_status, d_status, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -670,12 +697,13 @@ int device_analysis(int nb, const int32_t* Ap, const int32_t* Aj, int k, int nsw
     CKH(hipMemcpy(dAp, Ap, (static_cast<size_t>(nb) + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
     CKH(hipMemcpy(dAj, Aj, static_cast<size_t>(nA) * sizeof(int32_t), hipMemcpyHostToDevice));
     int64_t nnz = 0;
-    bilu_status st = sym_count(nb, dAp, dAj, k, dPp, &nnz, s);
+    int32_t nnzA = 0;
+    bilu_status st = sym_count(nb, dAp, dAj, k, dPp, &nnz, &nnzA, s);
     if (st != BILU_OK) return st;
     int32_t* dPj = sc.get<int32_t>(static_cast<size_t>(nnz));
     int32_t* dPl = sc.get<int32_t>(static_cast<size_t>(nnz));
     if (!dPj || !dPl) return BILU_ERR_ALLOC;
-    st = sym_write(nb, dAp, dAj, k, dPp, dPj, dPl, s);
+    st = sym_write(nb, nnzA, dAp, dAj, k, dPp, dPj, dPl, s);
     if (st != BILU_OK) return st;
     Pp.resize(static_cast<size_t>(nb) + 1);
     Pj.resize(static_cast<size_t>(nnz));
@@ -708,11 +736,12 @@ bilu_status bilu_symbolic_device(int nb, const int32_t* Ap, const int32_t* Aj, i
 {
     if (nb < 1 || k < 0 || k > 250 || !Ap || !Aj || !Pp || !nnzb || cap < 0) return BILU_ERR_ARG;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const bilu_status st = sym_count(nb, Ap, Aj, k, Pp, nnzb, s);
+    int32_t nnzA = 0;
+    const bilu_status st = sym_count(nb, Ap, Aj, k, Pp, nnzb, &nnzA, s);
     if (st != BILU_OK) return st;
     if (!Pj && !lev && cap == 0) return BILU_OK;   // size query
     if (!Pj || !lev || cap < *nnzb) return BILU_ERR_ARG;
-    return sym_write(nb, Ap, Aj, k, Pp, Pj, lev, s);
+    return sym_write(nb, nnzA, Ap, Aj, k, Pp, Pj, lev, s);
 }
 
 bilu_status bilu_levels_device(int nb, const int32_t* Pp, const int32_t* Pj, int sweep, int32_t* lvl,
