@@ -289,12 +289,22 @@ __device__ __forceinline__ void coherent_store_i(int* p, int v)
 // every round by 8 wavefronts a compute unit, 1.6, 2.4 and 3.6 so; with 8
 // wavefronts of this kernel 2.4, 3.6 and 5.5, with 32 2.0, 3.4 and 5.5.
 constexpr int kLevelSlots = 12;      // rows polled at once
-constexpr int kLevelStage = 32;      // rows listed before the first wait
+constexpr int kLevelStage = 36;      // rows listed before the first wait: ILU(4) on 7 points reads 35
 
+// Lists of columns (LISTS) come in the order in which k_col_fill's atomics hand
+// out places, about ascending, and a wait for the first entries of a long list
+// leaves the others to be read when it is over.  There the near rows come first
+// once a list has more than one round's entries, and of the rows that do not fit
+// the first kLevelStage those already published are not listed at all.  L^T, 27
+// points, 10^3, k = 2 and 3 (rows that read up to 57 and 91): 1.53 and 2.43 ms
+// with a cursor in the list, 3.34 and 6.74 ms far first and listed, 1.08 and
+// 1.77 ms so; 7 points, 60^3, k = 4, 14.0, 18.9 and 7.5 ms.
+template <bool LISTS>
 __global__ __launch_bounds__(256, 4) void k_levels(int nb, const int32_t* __restrict__ ptr,
                                                    const int32_t* __restrict__ idx, int mode, int forward, int* lvl,
                                                    unsigned int* ticket, int* status)
 {
+    constexpr int kFetch = LISTS ? 8 : 4;
     __shared__ int wl[4][64];
     __shared__ int wstage[4][kLevelStage][64];
     const int lane = threadIdx.x & 63;
@@ -313,6 +323,8 @@ __global__ __launch_bounds__(256, 4) void k_levels(int nb, const int32_t* __rest
         int e = done ? 0 : ptr[row];
         const int e1 = done ? 0 : ptr[row + 1];
         const int ends = e + e1 - 1;
+        const bool turned = (forward == 0) != (LISTS && e1 - e > kLevelSlots);
+        bool again = false;            // entries were listed before
         int best = -1;
         int dep[kLevelSlots];          // a row of another wavefront, or a lane of this one
         unsigned int pend = 0, local = 0, slots = 0;
@@ -321,20 +333,27 @@ __global__ __launch_bounds__(256, 4) void k_levels(int nb, const int32_t* __rest
         auto fetch = [&]() {
             staged = taken = 0;
             while (e < e1 && staged < kLevelStage) {
-                int j[4];
+                int j[kFetch], lv[kFetch];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kFetch; ++u) {
                     const int at = min(e + u, e1 - 1);
-                    j[u] = idx[forward ? at : ends - at];
+                    j[u] = idx[turned ? ends - at : at];
+                    lv[u] = -1;
+                }
+                if (LISTS && again) {
+#pragma unroll
+                    for (int u = 0; u < kFetch; ++u) lv[u] = coherent_load_i(lvl + j[u]);
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kFetch; ++u) {
                     if (e < e1 && staged < kLevelStage) {
-                        if (mode == 2 || (mode == 0 ? j[u] < row : j[u] > row)) stage[staged++][lane] = j[u];
+                        if (LISTS && lv[u] != -1) best = max(best, lv[u]);
+                        else if (LISTS || (mode == 0 ? j[u] < row : j[u] > row)) stage[staged++][lane] = j[u];
                         ++e;
                     }
                 }
             }
+            again = true;
         };
         // the next of the stage, into registers
         auto refill = [&]() {
@@ -647,8 +666,9 @@ bilu_status levels_impl(int nb, const int32_t* Pp, const int32_t* Pj, int sweep,
     // persistent: at most as many wavefronts as there are row groups
     const int groups = static_cast<int>((static_cast<int64_t>(nb) + 63) / 64);
     const int wg = std::max(1, std::min((groups + 3) / 4, 1024));
-    k_levels<<<wg, 256, 0, s>>>(nb, ptr, idx, mode, forward ? 1 : 0, lvl,
-                                reinterpret_cast<unsigned int*>(d_small + 2), d_small);
+    unsigned int* ticket = reinterpret_cast<unsigned int*>(d_small + 2);
+    if (mode == 2) k_levels<true><<<wg, 256, 0, s>>>(nb, ptr, idx, mode, forward ? 1 : 0, lvl, ticket, d_small);
+    else k_levels<false><<<wg, 256, 0, s>>>(nb, ptr, idx, mode, forward ? 1 : 0, lvl, ticket, d_small);
     int32_t* rows_in = sc.get<int32_t>(static_cast<size_t>(nb));
     int32_t* keys_out = sc.get<int32_t>(static_cast<size_t>(nb));
     if (!rows_in || !keys_out) return BILU_ERR_ALLOC;

@@ -1,7 +1,8 @@
 """GPU symbolic phase on patterns of enough rows for the small tables: grids of
-7 and 27 points and chains with hubs, whose rows fit and outgrow every table.
-Integer work: equal to the oracle.  A search given up for a larger table, or run
-in the wrong one, costs a bounded part of the search."""
+7 and 27 points and chains with hubs, whose rows fit and outgrow every table, and
+level sets of long lists of rows and columns.  Integer work: equal to the oracle.
+A search given up for a larger table costs a bounded part of the search, and
+lists of columns no more than lists of rows."""
 import time
 
 import numpy as np
@@ -11,6 +12,7 @@ import torch
 from paper_1703_01325_amd import synth
 
 from test_gpu_symbolic import api, check_vs_oracle, cuda_i32  # noqa: F401
+from test_gpu_symbolic_tables import wide_row_pattern
 
 pytestmark = pytest.mark.gpu
 
@@ -86,3 +88,22 @@ def test_search_cost_of_wide_rows(api):  # noqa: F811
     the time of k = 0; a table filled to its last slot first made it 30 times."""
     Ap, Aj = (cuda_i32(a) for a in stencil27_pattern(10))
     assert _seconds(lambda: api.symbolic_device(Ap, Aj, 3)) < 8 * _seconds(lambda: api.symbolic_device(Ap, Aj, 0))
+
+
+def test_level_cost_of_long_column_lists(api):  # noqa: F811
+    """27 points, k = 4: the level sets of L^T, whose lists come in no certain
+    order, take about 0.6 of those of L; waiting for them entry by entry in that
+    order they took twice as long."""
+    Ap, Aj = (cuda_i32(a) for a in stencil27_pattern(10))
+    Pp, Pj, _ = api.symbolic_device(Ap, Aj, 4)
+    assert _seconds(lambda: api.levels_device(Pp, Pj, 3)) < 1.3 * _seconds(lambda: api.levels_device(Pp, Pj, 0))
+
+
+@pytest.mark.parametrize("width", [35, 36, 37, 71, 72, 73, 109])
+def test_list_edges(api, oracle_mod, width):  # noqa: F811
+    """Lists of about as many rows as are listed at a time, and twice and three
+    times as many."""
+    nb = 2 * width + 5
+    Ap, Aj = wide_row_pattern(nb, width)
+    for k in (0, 2):
+        check_vs_oracle(api, oracle_mod, f"wide{width}", nb, Ap, Aj, k)
