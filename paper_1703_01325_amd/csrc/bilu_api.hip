@@ -1478,18 +1478,33 @@ static bilu_status run_sweep_gen(bilu_ctx* c, int which, const double* rhs, doub
     // (32 KiB each; the blocks past them come after the first have been used)
     a.stage = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(c->gen_blocks, 32768 / bb8)));
     const size_t lds = static_cast<size_t>(a.stage) * (bb8 + 8 * h.bs);
-    // wavefronts for the rows of six levels, one to four a compute unit: enough
+    // wavefronts for the rows of six levels, one to 16 a compute unit: enough
     // to have blocks staged before their turn, few enough not to hinder the
     // others' polls (one application, us, with 1, 2, 4 and 8 a compute unit:
     // 12^3 b = 25, 51 rows a level, 165, 173, 186, 203; 24^3 b = 25, 197 rows a
-    // level, 939, 574, 503, 531)
+    // level, 939, 574, 503, 531).  A ticket takes 12 ns, whoever draws it: where
+    // there are wavefronts enough, four or eight take their rows by one (24^3
+    // b = 25 503 -> 416 us; 64^3 b = 9, 1380 rows a level, with 1, 4 and 8 rows a
+    // ticket 6389, 1748 and 1046 us, as point rows 2336), and each several one after
+    // the other where a level gives all of them as many (20000 rows a level, b = 9:
+    // 205 -> 128 us, as point rows 145)
     const int64_t ahead = 6LL * h.nb / std::max(1, h.sweep[which].nlev);
-    const int per_cu = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(4, ahead / std::max(1, c->num_cu))));
-    const int blocks = persistent_blocks(c, h.nb, 1, per_cu);
-    a.total_waves = static_cast<unsigned int>(blocks);
+    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(16, ahead / std::max(1, c->num_cu)));
+    a.turns = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(16, ahead / (6 * 16 * std::max(1, c->num_cu)))));
     a.spin_limit = c->spin_limit;
-    if (upper) hipLaunchKernelGGL(dev::k_sweep_rows_gen<true>, dim3(blocks), dim3(64), lds, s, a);
-    else hipLaunchKernelGGL(dev::k_sweep_rows_gen<false>, dim3(blocks), dim3(64), lds, s, a);
+    const auto launch = [&](auto kernel, int rows, int64_t waves) {
+        const int blocks = persistent_blocks(c, h.nb, rows * a.turns, static_cast<int>(waves) / rows);
+        a.total_waves = static_cast<unsigned int>(blocks);
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * rows), rows * lds, s, a);
+    };
+    using namespace dev;
+    if (per_cu >= 8 && 8 * lds <= 65536) {
+        launch(upper ? k_sweep_rows_gen<true, 8> : k_sweep_rows_gen<false, 8>, 8, per_cu);
+    } else if (per_cu >= 4 && 4 * lds <= 65536) {
+        launch(upper ? k_sweep_rows_gen<true, 4> : k_sweep_rows_gen<false, 4>, 4, per_cu);
+    } else {
+        launch(upper ? k_sweep_rows_gen<true, 1> : k_sweep_rows_gen<false, 1>, 1, std::min<int64_t>(4, per_cu));
+    }
     timing_end(c, tslot, s);
     CK(hipGetLastError());
     return BILU_OK;

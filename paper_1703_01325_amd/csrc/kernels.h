@@ -865,15 +865,16 @@ __global__ void k_block_dinv_gen(int64_t nb, int bs, const double* __restrict__ 
 }
 
 // Sweep of L (UPPER = false) or U' (true: of D^{-1} rhs) by block rows, one
-// right-hand side: a wavefront takes a row from a ticket in level order, lane r
-// its component r.  The row's blocks (consecutive in memory) come to LDS before
+// right-hand side: a workgroup takes NW * turns rows (see run_sweep_gen) from a
+// ticket in level order, each of its NW wavefronts one at a time, lane r its
+// component r.  The row's blocks (consecutive in memory) come to LDS before
 // the wait for the rows it reads, `stage` blocks at a time; those rows are
 // polled all at once (out starts at kNotReady and receives each value once,
 // see await_value), and the products run over the blocks in order, components
 // in order, as the point rows do.  A level's latency is all that counts: 34
 // levels of 12^3, bs = 25, ILU(0) took 300 us as point rows, whose 75
 // dependencies a row went through the row tiles, and take 83 us so; 24^3 800
-// and 250 us.
+// and 208 us.
 struct GenSweepArgs {
     const int32_t* rows;      // block rows in level order
     const int32_t* Pp;
@@ -891,58 +892,82 @@ struct GenSweepArgs {
     int bs;
     int nrows;
     int stage;                // blocks in LDS
-    unsigned int total_waves;
+    int turns;                // rows of a ticket that a wavefront takes, one after the other
+    unsigned int total_waves; // workgroups
     unsigned int spin_limit;
 };
 
-template <bool UPPER>
-__global__ __launch_bounds__(64) void k_sweep_rows_gen(GenSweepArgs a)
+template <bool UPPER, int NW>
+__global__ __launch_bounds__(64 * NW) void k_sweep_rows_gen(GenSweepArgs a)
 {
     extern __shared__ double gsm[];
+    __shared__ int s_first;
     if (gated_off(a.gate)) return;
     const int bs = a.bs, bb = bs * bs;
-    double* sF = gsm;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    double* sF = gsm + wave * (a.stage * (bb + bs));
     double* sY = sF + a.stage * bb;      // stage * bs, or the row's right-hand side
     const int lane = lane_id();
     const int r = lane < bs ? lane : 0;
-    for (int tk = __builtin_amdgcn_readfirstlane(grab_ticket(a.ticket)); tk < a.nrows;
-         tk = __builtin_amdgcn_readfirstlane(grab_ticket(a.ticket))) {
-        const int i = uniform_load(a.rows, tk);
-        const int d = uniform_load(a.Pdiag, i);
-        const int e0 = UPPER ? d + 1 : uniform_load(a.Pp, i);
-        const int e1 = UPPER ? uniform_load(a.Pp, i + 1) : d;
-        const int64_t i0 = static_cast<int64_t>(i) * bs;
-        double acc = a.rhs[i0 + r];
-        if (lane < bs) a.reset[i0 + lane] = not_ready();
-        if (UPPER) {
-            if (lane < bs) sY[lane] = acc;
+    // the wavefront's own LDS, written and read by its lanes
+    auto exchanged = []() {
+        if constexpr (NW == 1) {
             __syncthreads();
-            const double* D = a.Dinv + static_cast<int64_t>(i) * bb;
-            acc = 0.0;
-#pragma unroll 8
-            for (int c = 0; c < bs; ++c) acc += D[c * bs + r] * sY[c];
-            __syncthreads();
+        } else {
+            __builtin_amdgcn_wave_barrier();
+            asm volatile("" ::: "memory");
         }
-        for (int eb = e0; eb < e1; eb += a.stage) {
-            const int n = min(a.stage, e1 - eb);
-            const double* F = a.vals + static_cast<int64_t>(eb) * bb;
+    };
+    for (;;) {
+        const int some = NW * a.turns;
+        if (threadIdx.x == 0) {
+            const unsigned long long t = atomicAdd(a.ticket, static_cast<unsigned long long>(some));
+            s_first = t > 0x3fffffffULL ? 0x3fffffff : static_cast<int>(t);
+        }
+        __syncthreads();
+        const int first = __builtin_amdgcn_readfirstlane(s_first);
+        __syncthreads();
+        if (first >= a.nrows) break;
+        // (a wavefront's rows ascend, so the first unfinished row of all is always
+        // in hand, and the launch drains)
+        for (int tk = first + wave; tk < min(first + some, a.nrows); tk += NW) {
+            const int i = uniform_load(a.rows, tk);
+            const int d = uniform_load(a.Pdiag, i);
+            const int e0 = UPPER ? d + 1 : uniform_load(a.Pp, i);
+            const int e1 = UPPER ? uniform_load(a.Pp, i + 1) : d;
+            const int64_t i0 = static_cast<int64_t>(i) * bs;
+            double acc = a.rhs[i0 + r];
+            if (lane < bs) a.reset[i0 + lane] = not_ready();
+            if (UPPER) {
+                if (lane < bs) sY[lane] = acc;
+                exchanged();
+                const double* D = a.Dinv + static_cast<int64_t>(i) * bb;
+                acc = 0.0;
+#pragma unroll 8
+                for (int c = 0; c < bs; ++c) acc += D[c * bs + r] * sY[c];
+                exchanged();
+            }
+            for (int eb = e0; eb < e1; eb += a.stage) {
+                const int n = min(a.stage, e1 - eb);
+                const double* F = a.vals + static_cast<int64_t>(eb) * bb;
 #pragma unroll 4
-            for (int x = lane; x < n * bb; x += 64) sF[x] = F[x];
-            for (int x = lane; x < n * bs; x += 64) {
-                const int k = x / bs;
-                const double* p = a.out + static_cast<int64_t>(a.Pj[eb + k]) * bs + (x - k * bs);
-                sY[x] = await_value(p, coherent_load(p), a.spin_limit, a.status);
-            }
-            __syncthreads();
-            for (int k = 0; k < n; ++k) {
+                for (int x = lane; x < n * bb; x += 64) sF[x] = F[x];
+                for (int x = lane; x < n * bs; x += 64) {
+                    const int k = x / bs;
+                    const double* p = a.out + static_cast<int64_t>(a.Pj[eb + k]) * bs + (x - k * bs);
+                    sY[x] = await_value(p, coherent_load(p), a.spin_limit, a.status);
+                }
+                exchanged();
+                for (int k = 0; k < n; ++k) {
 #pragma unroll 8
-                for (int u = 0; u < bs; ++u) acc -= sF[k * bb + u * bs + r] * sY[k * bs + u];
+                    for (int u = 0; u < bs; ++u) acc -= sF[k * bb + u * bs + r] * sY[k * bs + u];
+                }
+                exchanged();
             }
-            __syncthreads();
+            if (lane < bs) coherent_store(a.out + i0 + lane, publishable(acc));
         }
-        if (lane < bs) coherent_store(a.out + i0 + lane, publishable(acc));
     }
-    finish_persistent(a.ticket, a.done, a.total_waves);
+    if (wave == 0) finish_persistent(a.ticket, a.done, a.total_waves);
 }
 
 // y = A x (or A^T x through the transposed structure), one right-hand side,
