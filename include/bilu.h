@@ -95,7 +95,8 @@ typedef struct {
     int nlev[4];          /* levels per sweep (0 if not built)     */
     int rows_per_chunk;   /* block rows per wavefront in the sweeps */
     int64_t sweep_slots[4]; /* padded block slots of each sweep layout */
-    int tile_rows;        /* block rows per tile of the tiled sweeps (0: not chosen yet) */
+    int tile_rows;        /* block rows per tile of the tiled sweeps (0: not chosen, as
+                             long as no sweep uses them; see bilu_get_sweep_info) */
     int tile_group;       /* tiles per workgroup of the tiled sweeps (1: one wavefront
                              per tile; see BILU_TUNE_TILE_GROUP)                         */
     int lds_ring[4];      /* per tiled sweep: chunks whose rows a wavefront keeps in LDS
@@ -158,6 +159,30 @@ bilu_status bilu_get_levels(const bilu_ctx* ctx, int sweep, int* nlev,
                             const int32_t** level_ptr, const int32_t** level_rows);
 
 bilu_status bilu_get_info(const bilu_ctx* ctx, bilu_info* info);
+
+/* Forms of a sweep launch. */
+typedef enum {
+    BILU_FORM_LEVELS = 0,   /* level chunks (BILU_TUNE_SWEEP_MODE 0 and 1)          */
+    BILU_FORM_TILES = 1,    /* row tiles                                            */
+    BILU_FORM_LINES = 2,    /* line sweeps (BILU_TUNE_LINE_SWEEP)                   */
+    BILU_FORM_PENCILS = 3,  /* blocks of grid lines                                 */
+    BILU_FORM_ROWS = 4      /* block rows (block sizes above 8)                     */
+} bilu_form;
+
+/* The two sweeps of an application (filled by bilu_get_sweep_info). */
+typedef struct {
+    int form[2];          /* bilu_form of the first and the second sweep            */
+    int width[2];         /* BILU_FORM_PENCILS: dependency slots of a row, else 0   */
+    int tiles[2];         /* BILU_FORM_PENCILS: blocks of grid lines, else 0        */
+    int columns[2];       /* BILU_FORM_PENCILS: columns a workgroup sweeps together,
+                             else 0 (and before the first factorisation)            */
+} bilu_sweep_info;
+
+/* How an application of nrhs columns (transpose = 1: of the transpose) would run
+ * with the knobs as they are (its layouts are formed on the host if they were
+ * not yet; nothing is launched).  Errors: BILU_ERR_ARG, BILU_ERR_STATE (transposed
+ * sweeps not built), BILU_ERR_ALLOC. */
+bilu_status bilu_get_sweep_info(bilu_ctx* ctx, int transpose, int nrhs, bilu_sweep_info* info);
 
 /*
  * Symbolic phase on the GPU (Algorithm 3 with Eq 1-2): the ILU(k) pattern P
@@ -542,6 +567,11 @@ typedef struct bilu_batch_tune_info {
     int reserved;
 } bilu_batch_tune_info;
 bilu_status bilu_batch_autotune(bilu_batch* batch, hipStream_t stream, bilu_batch_tune_info* info);
+
+/* *form: BILU_FORM_PENCILS or BILU_FORM_TILES, whichever the batch's sweeps take
+ * (pencils where every member is a grid with ILU(0) rows and no other tile scale
+ * was chosen). */
+bilu_status bilu_batch_get_form(const bilu_batch* batch, int* form);
 
 /* Member s as a single-system context (owned by the batch: do not destroy),
  * e.g. for bilu_get_factors. */

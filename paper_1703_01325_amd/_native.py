@@ -27,14 +27,15 @@ DEVICE_SYMBOLIC = 2
 
 # every symbol declared in include/bilu.h
 EXPORTS = (
-    "bilu_analyze", "bilu_get_pattern", "bilu_get_levels", "bilu_get_info", "bilu_validate",
+    "bilu_analyze", "bilu_get_pattern", "bilu_get_levels", "bilu_get_info", "bilu_get_sweep_info", "bilu_validate",
     "bilu_symbolic_device", "bilu_levels_device",
     "bilu_factor_numeric", "bilu_factor_diag", "bilu_get_factors", "bilu_get_factors_f32",
     "bilu_apply", "bilu_apply_noalloc", "bilu_apply_point", "bilu_apply_transpose", "bilu_spmv", "bilu_solve", "bilu_grad_A",
     "bilu_tune", "bilu_autotune", "bilu_check", "bilu_timing", "bilu_timing_read",
     "bilu_destroy", "bilu_status_string",
     "bilu_batch_create", "bilu_batch_offsets", "bilu_batch_factor", "bilu_batch_apply",
-    "bilu_batch_spmv", "bilu_batch_solve", "bilu_batch_autotune", "bilu_batch_member", "bilu_batch_destroy",
+    "bilu_batch_spmv", "bilu_batch_solve", "bilu_batch_autotune", "bilu_batch_get_form", "bilu_batch_member",
+    "bilu_batch_destroy",
 )
 K_SWEEP_L, K_SWEEP_U, K_SWEEP_UT, K_SWEEP_LT, K_SPMV, K_FACTOR, K_SPLIT, K_SWEEP_U_SPMV, K_COUNT = range(9)
 K_NAMES = ("sweep_L", "sweep_U", "sweep_UT", "sweep_LT", "spmv", "factor", "split", "sweep_U_spmv")
@@ -47,6 +48,13 @@ class BiluInfo(ct.Structure):
                 ("sweep_slots", ct.c_int64 * 4), ("tile_rows", ct.c_int),
                 ("tile_group", ct.c_int), ("lds_ring", ct.c_int * 4), ("tile_block", ct.c_int * 4),
                 ("line_sweep", ct.c_int * 2)]
+
+
+FORM_NAMES = ("levels", "tiles", "lines", "pencils", "rows")
+
+
+class SweepInfo(ct.Structure):
+    _fields_ = [("form", ct.c_int * 2), ("width", ct.c_int * 2), ("tiles", ct.c_int * 2), ("columns", ct.c_int * 2)]
 
 
 class KernelTime(ct.Structure):
@@ -94,6 +102,7 @@ def _load():
     L.bilu_get_pattern.argtypes = [VP, ct.POINTER(ct.c_int64), ct.POINTER(P), ct.POINTER(P), ct.POINTER(P)]
     L.bilu_get_levels.argtypes = [VP, I, ct.POINTER(I), ct.POINTER(P), ct.POINTER(P)]
     L.bilu_get_info.argtypes = [VP, ct.POINTER(BiluInfo)]
+    L.bilu_get_sweep_info.argtypes = [VP, I, I, ct.POINTER(SweepInfo)]
     L.bilu_validate.argtypes = [VP]
     L.bilu_symbolic_device.argtypes = [I, P, P, I, P, P, P, ct.c_int64, ct.POINTER(ct.c_int64), P]
     L.bilu_levels_device.argtypes = [I, P, P, I, P, P, P, ct.POINTER(I), P]
@@ -124,6 +133,7 @@ def _load():
     L.bilu_batch_spmv.argtypes = [VP, P, P, P]
     L.bilu_batch_solve.argtypes = [VP, P, P, ct.POINTER(SolveOpts), ct.POINTER(RhsInfo), P]
     L.bilu_batch_autotune.argtypes = [VP, P, ct.POINTER(BatchTuneInfo)]
+    L.bilu_batch_get_form.argtypes = [VP, ct.POINTER(I)]
     L.bilu_batch_member.argtypes = [VP, I, ct.POINTER(VP)]
     L.bilu_batch_destroy.argtypes = [VP]
     L.bilu_batch_destroy.restype = None
@@ -210,6 +220,13 @@ def bilu_get_info(ctx):
     info = BiluInfo()
     _check(lib.bilu_get_info(ctx, ct.byref(info)), "bilu_get_info")
     return info
+
+
+def bilu_get_sweep_info(ctx, transpose, nrhs):
+    info = SweepInfo()
+    _check(lib.bilu_get_sweep_info(ctx, int(transpose), int(nrhs), ct.byref(info)), "bilu_get_sweep_info")
+    return {"form": tuple(FORM_NAMES[f] for f in info.form), "width": tuple(info.width),
+            "tiles": tuple(info.tiles), "columns": tuple(info.columns)}
 
 
 def bilu_validate(ctx):
@@ -369,6 +386,12 @@ def bilu_batch_autotune(batch, stream):
     _check(lib.bilu_batch_autotune(batch, ct.c_void_p(stream), ct.byref(info)), "bilu_batch_autotune")
     return {"tile_scale": info.tile_scale, "pair_us": info.pair_us, "default_us": info.default_us,
             "candidates": info.candidates}
+
+
+def bilu_batch_get_form(batch):
+    form = ct.c_int()
+    _check(lib.bilu_batch_get_form(batch, ct.byref(form)), "bilu_batch_get_form")
+    return FORM_NAMES[form.value]
 
 
 def bilu_batch_member(batch, s):

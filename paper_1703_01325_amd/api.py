@@ -81,6 +81,12 @@ class BlockILU:
     def info(self):
         return N.bilu_get_info(self._ctx)
 
+    def sweep_info(self, nrhs: int = 1, transpose=False):
+        """How the two sweeps of an application of ``nrhs`` columns run: their
+        ``form`` ("pencils" on grid patterns, "tiles", "levels", "lines", "rows")
+        and, for pencils, ``width``, ``tiles`` and ``columns``."""
+        return N.bilu_get_sweep_info(self._ctx, transpose, nrhs)
+
     def pattern(self):
         return N.bilu_get_pattern(self._ctx)
 
@@ -278,6 +284,10 @@ class BlockILUBatch:
     def autotune(self):
         """Device-timed choice of the members' tile sizes (results unchanged)."""
         return N.bilu_batch_autotune(self._b, _stream())
+
+    def sweep_form(self):
+        """"pencils" or "tiles": what the batch's sweeps take."""
+        return N.bilu_batch_get_form(self._b)
 
     def member(self, s: int) -> BlockILU:
         """Member s as a BlockILU view (owned by the batch)."""

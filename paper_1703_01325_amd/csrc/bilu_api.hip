@@ -1746,6 +1746,36 @@ bilu_status bilu_get_info(const bilu_ctx* c, bilu_info* info)
     return BILU_OK;
 }
 
+bilu_status bilu_get_sweep_info(bilu_ctx* c, int transpose, int nrhs, bilu_sweep_info* info)
+try {
+    if (!c || !info || nrhs < 1 || nrhs > dev::kMaxRhs || (c->h.bs > kMaxKernelBs && (nrhs != 1 || transpose)))
+        return BILU_ERR_ARG;
+    std::memset(info, 0, sizeof(*info));
+    const bool tr = transpose != 0;
+    const int which[2] = {tr ? BILU_SWEEP_UT : BILU_SWEEP_L, tr ? BILU_SWEEP_LT : BILU_SWEEP_U};
+    if (!c->h.sweep[which[0]].built || !c->h.sweep[which[1]].built) return BILU_ERR_STATE;
+    const bool pencil = use_pencil(c, tr, nrhs);
+    for (int i = 0; i < 2; ++i) {
+        const int w = which[i];
+        if (c->h.bs > kMaxKernelBs) {
+            info->form[i] = BILU_FORM_ROWS;
+        } else if (pencil) {
+            const HostPencil& hp = c->h.pencil[w];
+            info->form[i] = BILU_FORM_PENCILS;
+            info->width[i] = hp.width;
+            info->tiles[i] = hp.ntiles;
+            info->columns[i] = c->dev_ready ? pencil_columns(c, hp, nrhs) : 0;
+        } else if (use_lines(c, w, nrhs)) {
+            info->form[i] = BILU_FORM_LINES;
+        } else {
+            info->form[i] = sweep_form(c, nrhs) == kFormTiled ? BILU_FORM_TILES : BILU_FORM_LEVELS;
+        }
+    }
+    return BILU_OK;
+} catch (const std::bad_alloc&) {
+    return BILU_ERR_ALLOC;
+}
+
 bilu_status bilu_validate(const bilu_ctx* c)
 try {
     if (!c) return BILU_ERR_ARG;
