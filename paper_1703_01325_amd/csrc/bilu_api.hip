@@ -146,6 +146,7 @@ struct bilu_ctx {
     DevPencil pencil[4];
     double* d_pw = nullptr;
     size_t pw_cap = 0;
+    bool batch_member = false;  // applied by its batch, in the batch's work space
 
     double* d_y = nullptr;      // intermediate of an application, kept at kNotReady
     size_t y_cap = 0;
@@ -1865,10 +1866,11 @@ try {
     for (DevPencil& d : c->pencil) d.vals_precision = -1;
     bilu_status st;
     if (use_pencil(c, false, 1)) {
-        // the transposed pair's layouts too, as the row tiles' are
+        // the transposed pair's layouts too, as the row tiles' are; the work space
+        // of a batch's member waits until it is applied by itself
         for (bool tr : {false, true})
             if (use_pencil(c, tr, 1) &&
-                ((st = layout_pencil(c, tr, s)) || (st = ensure_pencil_work(c, tr, 1, s))))
+                ((st = layout_pencil(c, tr, s)) || (!c->batch_member && (st = ensure_pencil_work(c, tr, 1, s)))))
                 return st;
     } else if ((st = layout_form(c, sweep_form(c, 1), s))) {
         return st;

@@ -118,3 +118,21 @@ def test_batch_member_and_layout(api, precision):  # noqa: F811
         assert torch.equal(P.apply(r), z)
     assert P.factor(Ax, precision=precision) is None and T.factor(Ax + [extra], precision=precision) is None
     assert torch.equal(P.apply(r), T.apply(_long(P, T, r))[:P.n])
+
+
+def test_batch_work_space(api):  # noqa: F811
+    """A member's own work space (its vector between the sweeps, two exchange
+    arrays) is there once the member is applied by itself, not before."""
+    members = [synth.reservoir(40, 41, 42, 8, seed=3), synth.reservoir(5, 6, 7, 2, seed=4)]
+    P = api.BlockILUBatch([(m.nb, m.bs, m.Ap, m.Aj) for m in members], 0)
+    assert P.factor([cuda(m.Ax) for m in members]) is None and P.sweep_form() == "pencils"
+    r = cuda(np.random.default_rng(5).standard_normal(P.n))
+    z = P.apply(r)
+    r0, z0 = r[:members[0].n].clone(), z[:members[0].n].clone()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    m = P.member(0)
+    out = m.apply(r0, out=torch.empty_like(z0))
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] >= 8 * members[0].n
+    assert torch.equal(out, z0) and torch.equal(P.apply(r), z)
