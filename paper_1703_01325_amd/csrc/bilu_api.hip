@@ -790,7 +790,7 @@ int64_t pencil_lds(const bilu_ctx* c, const HostPencil& hp, int cb)
 int pencil_columns(const bilu_ctx* c, const HostPencil& hp, int ncol)
 {
     const bool full = static_cast<int64_t>(hp.ntiles) * ncol >= int64_t(6) * c->num_cu;
-    return ncol % 2 == 0 && full && hp.width <= kPencilPairWidth && pencil_lds(c, hp, 2) <= c->lds_max ? 2 : 1;
+    return ncol % 2 == 0 && full && hp.width <= kPencilPairWidth && pencil_fits(hp, c->h.bs, 2, c->lds_max) ? 2 : 1;
 }
 
 bool use_lines(const bilu_ctx* c, int which, int R)
@@ -902,7 +902,7 @@ bool use_pencil(bilu_ctx* c, bool transpose, int R)
     for (int w : {transpose ? BILU_SWEEP_UT : BILU_SWEEP_L, transpose ? BILU_SWEEP_LT : BILU_SWEEP_U}) {
         if (!c->h.sweep[w].built) return false;
         const HostPencil& hp = host_pencil(c->h, w);
-        if (!hp.built || pencil_lds(c, hp, 1) > c->lds_max) return false;
+        if (!hp.built || !pencil_fits(hp, c->h.bs, 1, c->lds_max)) return false;
     }
     return true;
 }

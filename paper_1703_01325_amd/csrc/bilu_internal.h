@@ -209,13 +209,24 @@ constexpr int pencil_list_rows(int rpc)
 
 constexpr int pencil_meta_quads(int width) { return ((width + 1) / 2 + 1 + 3) / 4; }
 
-// LDS of a workgroup that sweeps cb columns: zero row, ring and fed rows, then
-// the ring's destinations, the feeder's list and the place of values that are
-// not kept.
+// LDS of a launch for workgroups that sweep cb columns: zero row, ring and fed
+// rows, then the ring's destinations, the feeder's list and the place of values
+// that are not kept.
 inline int64_t pencil_lds_bytes(int ring, int ext_ring, int rpc, int bs, int cb)
 {
     return static_cast<int64_t>(kPencilZeroBytes + ring * kPencilSlotBytes + ext_ring * bs * 8) * cb +
            ring * kPencilSlotBytes + pencil_list_rows(rpc) * 16 + kPencilSlotBytes * cb;
+}
+
+// What the kernels hold in LDS besides: the sweep's progress, a copy a lane, and
+// five counts.
+constexpr int kPencilCounts = 5;
+constexpr int kPencilStaticBytes = (kWave + kPencilCounts) * 4;
+
+// Whether workgroups of cb columns fit where one may have `limit` bytes of LDS.
+inline bool pencil_fits(const HostPencil& s, int bs, int cb, int64_t limit)
+{
+    return pencil_lds_bytes(s.ring, s.ext_ring, s.rpc, bs, cb) + kPencilStaticBytes <= limit;
 }
 
 // Dependency slots of the pencil kernels that exist for block size bs, the

@@ -671,7 +671,7 @@ template <int B, typename T, int K, int CB, bool FUSE>
 __global__ __launch_bounds__(256, (PencilRec<B, T, K>::waves(CB))) void k_sweep_pencil(PencilArgs a)
 {
     extern __shared__ double2 pencil_lds[];
-    __shared__ int s_swept[64], s_count[5];
+    __shared__ int s_swept[kWave], s_count[kPencilCounts];
     if (gated_off(a.gate)) return;
     const PencilLds l = pencil_lds_map<B, CB>(a, reinterpret_cast<char*>(pencil_lds), s_swept, s_count);
     int& s_ticket = s_count[4];
@@ -744,7 +744,7 @@ template <typename T, bool FUSE>
 __global__ __launch_bounds__(256, 2) void k_sweep_pencil_batch(PencilBatchArgs b)
 {
     extern __shared__ double2 pencil_lds[];
-    __shared__ int s_swept[64], s_count[5];
+    __shared__ int s_swept[kWave], s_count[kPencilCounts];
     if (gated_off(b.gate)) return;
     char* base = reinterpret_cast<char*>(pencil_lds);
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);

@@ -1,6 +1,7 @@
 """The host self-check of the pencil layouts refuses layouts whose rows read
 their dependencies out of order or one of them twice (a small program around
-the host sources plants the faults)."""
+the host sources plants the faults), and a layout counts as fitting only with the
+LDS that its kernels hold besides the launch's."""
 import os
 import subprocess
 
@@ -59,6 +60,11 @@ int main(int argc, char** argv)
         HostPencil s;
         build_pencil(h, w, h.rpc, s);
         if (!s.built || validate_pencil(h, s) != BILU_OK) return 3;
+        // the LDS of a launch and the kernels' own, to the byte
+        for (int cb : {1, 2}) {
+            const int64_t all = pencil_lds_bytes(s.ring, s.ext_ring, s.rpc, bs, cb) + (64 + 5) * 4;
+            if (!pencil_fits(s, bs, cb, all) || pencil_fits(s, bs, cb, all - 1)) return 6;
+        }
         for (int c = 0; c < s.nchunks; ++c)
             for (int q = 0; q < s.rpc; ++q) {
                 const size_t a = static_cast<size_t>(c) * s.width * s.rpc + q, b = a + s.rpc;
@@ -97,5 +103,5 @@ def driver(tmp_path_factory):
                          ids=["b3k0", "b8k1", "b2k2"])
 def test_self_check_refuses_disorder_and_repeats(driver, args):
     r = subprocess.run([driver, *map(str, args)], capture_output=True, text=True, timeout=120)
-    assert r.returncode == 0, r.returncode     # 3: not built, 4: swapped slots pass, 5: a repeated slot passes
+    assert r.returncode == 0, r.returncode     # 3: not built, 4: swapped slots pass, 5: a repeated slot passes, 6: LDS
     assert int(r.stdout) > 100
