@@ -304,11 +304,11 @@ bilu_status bilu_apply_point(bilu_ctx* ctx, const double* r, double* z, hipStrea
  * bilu_apply for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same kernels and the same result bits as bilu_apply, with the
- * intermediate vector and everything else the sweeps write besides z in a
- * fixed 96 MiB scratch array of the library (one per device, held until the
- * process ends), so that a captured call stays good whatever is called on the
- * context between replays, short of new layouts, another factor precision or
- * bilu_destroy;
+ * intermediate vector and everything else the sweeps write besides z in fixed
+ * scratch arrays of the library (32 MiB per device, and 64 MiB more once a system
+ * is swept by blocks of grid lines; held until the process ends), so that a
+ * captured call stays good whatever is called on the context between replays,
+ * short of new layouts, another factor precision or bilu_destroy;
  * calls no hipMalloc, hipFree or allocating routine.  nb*bs*nrhs doubles must fit
  * in 32 MiB - 256 bytes, else BILU_ERR_ARG.  The layouts must already hold
  * the current factors (they do after bilu_factor_diag for nrhs = 1, or after

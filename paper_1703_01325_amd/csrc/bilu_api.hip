@@ -51,12 +51,11 @@ constexpr int kMaxTileDoubles = 8192;   // LDS of one tiled wavefront: 64 KiB
 // Scratch of bilu_apply_noalloc, one copy per device for the life of the
 // process: bytes [0, 8) ticket, [8, 12) done count and [12, 16) status of the
 // persistent sweeps, from byte kScratchHeader the intermediate vector y of
-// the application, from byte kScratchVector the exchange arrays of its two
-// pencil sweeps (each at most as long as y).  Host code uses the address
-// hipGetSymbolAddress gives for the current device, never the symbol itself.
+// the application.  Host code uses the address hipGetSymbolAddress gives for
+// the current device, never the symbol itself.
+constexpr size_t kScratchBytes = size_t(32) << 20;
 constexpr size_t kScratchHeader = 256;
-constexpr size_t kScratchVector = size_t(32) << 20;
-static __device__ __align__(256) unsigned char scratch[3 * kScratchVector];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 constexpr int kScratchDevices = 64;
@@ -77,6 +76,28 @@ bilu_status scratch_of_device(int device, unsigned char** out)
     *out = g_scratch_addr[device];
     return BILU_OK;
 }
+
+// The exchange arrays of bilu_apply_noalloc's two pencil sweeps, each at most as
+// long as y: one copy per device as well, allocated (allocate = true) with the
+// first pencil layouts of a system the call takes, and there from then on.  (As
+// part of the array above they made the library's first use 25 ms longer.)
+double* g_exchange[kScratchDevices] = {};
+
+bilu_status exchange_of_device(int device, bool allocate, double** out)
+{
+    if (device < 0 || device >= kScratchDevices) return BILU_ERR_ARG;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    if (!g_exchange[device] && allocate) {
+        void* p = nullptr;
+        if (hipMalloc(&p, 2 * kScratchBytes) != hipSuccess) return BILU_ERR_ALLOC;
+        g_exchange[device] = static_cast<double*>(p);
+    }
+    *out = g_exchange[device];
+    return *out ? BILU_OK : BILU_ERR_STATE;
+}
+
+// Whether bilu_apply_noalloc takes n unknowns.
+bool scratch_holds(int64_t n) { return static_cast<size_t>(n) * sizeof(double) <= kScratchBytes - kScratchHeader; }
 }  // namespace
 
 struct bilu_ctx {
@@ -933,6 +954,10 @@ bilu_status layout_pencil(bilu_ctx* c, bool transpose, hipStream_t s)
                                  (e - hp.ext_ptr[t]) % hp.ext_ring * bs * 8;
                     ext[i + 2] = hp.ext_free[e];
                 }
+            double* exch = nullptr;
+            if (!transpose && scratch_holds(static_cast<int64_t>(c->h.nb) * bs) &&
+                (st = exchange_of_device(c->device, true, &exch)))
+                return st;
             if ((st = upload(c, &d.ext_ptr, hp.ext_ptr)) || (st = upload(c, &d.rows, rows)) ||
                 (st = upload(c, &d.meta, hp.meta)) || (st = upload(c, &d.src, hp.src)) ||
                 (st = upload(c, &d.ext, ext)) || (st = upload(c, &d.tile_ptr, hp.tile_ptr)))
@@ -1943,7 +1968,7 @@ bilu_status bilu_apply_noalloc(bilu_ctx* c, const double* r, double* z, int nrhs
 {
     if (!c || !r || !z || nrhs < 1 || nrhs > dev::kMaxRhs || r == z || c->h.bs > kMaxKernelBs) return BILU_ERR_ARG;
     const int64_t ny = static_cast<int64_t>(c->h.nb) * c->h.bs * nrhs;
-    if (static_cast<size_t>(ny) * sizeof(double) > kScratchVector - kScratchHeader) return BILU_ERR_ARG;
+    if (!scratch_holds(ny)) return BILU_ERR_ARG;
     if (!c->dev_ready || !c->split_done) return BILU_ERR_STATE;
     // the layouts must already hold the current factors: laying them out would
     // allocate
@@ -1974,7 +1999,8 @@ bilu_status bilu_apply_noalloc(bilu_ctx* c, const double* r, double* z, int nrhs
         const int64_t first = c->h.pencil[BILU_SWEEP_L].nexch * c->h.bs * nrhs;
         const int64_t both = first + c->h.pencil[BILU_SWEEP_U].nexch * c->h.bs * nrhs;
         if (both > 2 * ny) return BILU_ERR_STATE;
-        double* exch = reinterpret_cast<double*>(base + kScratchVector);
+        double* exch = nullptr;
+        if ((st = exchange_of_device(device, false, &exch))) return st;
         PencilWork wk{y, {}, sync};
         wk.exch[BILU_SWEEP_L] = exch;
         wk.exch[BILU_SWEEP_U] = exch + first;
