@@ -130,9 +130,9 @@ typedef struct {
  * level sets of Eq 4, then the layouts of the sweeps.  On the host (needs no
  * GPU) unless flags has BILU_DEVICE_SYMBOLIC.
  *   nb, bs   block rows (>= 1) and block size (1..32).  Sizes 1..8 have
- *            block-row sweep and SpMV kernels; 9..32 (the large blocks of
- *            Section 3, Table 2) factor by blocks, sweep at point
- *            granularity (bilu_apply_point) and take one right-hand side,
+ *            kernels of their own; 9..32 (the large blocks of Section 3,
+ *            Table 2) run kernels with a run-time block size, factorisation
+ *            and sweeps by block rows, and take one right-hand side,
  *            FP64 factors, no transposed solve, no batch, no autotune, no
  *            bilu_apply_noalloc (BILU_ERR_ARG there)
  *   Ap, Aj   host block-CSR pattern of A (borrowed, copied)

@@ -162,8 +162,8 @@ struct bilu_ctx {
     bool form_uploaded[kForms] = {false, false, false};
     int line_block = 0;         // line sweep of L and U' with blocks ny + 256*nz (0: off)
     bool layouts_checked = false;   // validate_layout passed on the layouts as built
-    // pencil sweeps (use_pencil): layouts, the vector between the two sweeps
-    // of an application, and off where a caller reads the row-tile layouts
+    // pencil sweeps (use_pencil): layouts and the vector between the two sweeps
+    // of an application
     DevPencil pencil[4];
     double* d_pw = nullptr;
     size_t pw_cap = 0;
@@ -788,10 +788,6 @@ bilu_status ensure_device(bilu_ctx* c)
     return BILU_OK;
 }
 
-// Layout form the sweeps use: row tiles in mode 2 (their vector accesses are
-// 31-bit byte offsets, so the (n x R) vectors must stay below 2 GiB), level
-// chunks otherwise.
-// Sweep `which` of R columns runs as a line sweep.
 int persistent_blocks(bilu_ctx* c, int units, int units_per_block, int per_cu)
 {
     const int want = std::max(1, (units + units_per_block - 1) / units_per_block);
@@ -814,11 +810,15 @@ int pencil_columns(const bilu_ctx* c, const HostPencil& hp, int ncol)
     return ncol % 2 == 0 && full && hp.width <= kPencilPairWidth && pencil_fits(hp, c->h.bs, 2, c->lds_max) ? 2 : 1;
 }
 
+// Sweep `which` of R columns runs as a line sweep.
 bool use_lines(const bilu_ctx* c, int which, int R)
 {
     return c->line_block > 0 && R == 1 && c->sweep_mode == 2 && c->h.lines[which].built;
 }
 
+// Layout form the sweeps use: row tiles in mode 2 (their vector accesses are
+// 31-bit byte offsets, so the (n x R) vectors must stay below 2 GiB), level
+// chunks otherwise.
 int sweep_form(const bilu_ctx* c, int R)
 {
     const bool fits = static_cast<int64_t>(c->h.nb) * c->h.bs * 8 * R <= static_cast<int64_t>(INT32_MAX);
@@ -892,8 +892,13 @@ bilu_status layout_form(bilu_ctx* c, int form, hipStream_t s)
 // An application runs as a pair of pencil sweeps where no layout was asked
 // for (every knob of the row tiles at its automatic value) and the pattern has
 // a pencil layout for both: grid lines in natural order and rows no wider than
-// the kernels.  Every pattern measured that has one ran faster that way (2 to
-// 7 times, figures at k_sweep_pencil), so there is no other condition.
+// the kernels.  A pair against the row tiles' pair on MI355X, grids of 2 x 2 x 2
+// to 120^3, flat, thin and long ones, b = 1..8, k = 0..3, 1 to 32 columns, both
+// precisions: 1.0 to 9 times faster, so there is no other condition.  Least is
+// gained where the kernel's values spill (see pencil_width): 15 x 120 x 120, b = 8,
+// k = 2 11997 -> 11649 us (its L sweep alone is slower, 5547 -> 5725), 20 x 120 x
+// 120, b = 6, k = 2 11873 -> 9417, 30 x 120 x 120, b = 4, k = 3 27341 -> 13483,
+// where 24 x 120 x 120, b = 5, k = 2, without spills, gains 12239 -> 2362.
 bool row_tiles_asked(const bilu_ctx* c)
 {
     return c->tile_rows_req != 0 || c->tile_group_req != 0 || c->tile_block != 0 || c->line_block != 0;

@@ -14,7 +14,7 @@ namespace bilu {
 constexpr int kWave = 64;          // CDNA wavefront width
 constexpr int kMaxBs = 32;          // block sizes the library accepts
 constexpr int kMaxKernelBs = 8;     // block sizes with block-row sweep and SpMV kernels;
-                                    // larger ones sweep at point granularity
+                                    // larger ones sweep by block rows of run-time size
 
 // Rows of a sweep grouped for the GPU: level by level (Eq 4), a level's rows
 // cut into chunks of `rpc` rows (one wavefront each), chunk c holding
@@ -231,8 +231,14 @@ inline bool pencil_fits(const HostPencil& s, int bs, int cb, int64_t limit)
 
 // Dependency slots of the pencil kernels that exist for block size bs, the
 // smallest that holds max_width (0: none): 3, 6, 11 and 21 are the widest rows
-// of ILU(0..3) on a 7-point grid.  Two chunks of a row's factor values at least
-// stay in registers, which 21 slots of blocks above 4 x 4 do not.
+// of ILU(0..3) on a 7-point grid.  The sweep wavefront holds two chunks of values
+// at least; 21 slots of blocks above 4 x 4 are far more than its 512 registers.
+// Past these, the FP64 kernels of 11 slots at b = 6 and 8 and of 21 at b = 3 and 4
+// spill 41 to 73 to scratch memory, those of 6 slots for two columns at b = 5, 7
+// and 8 26 to 59; in FP32 those of 11 slots at b = 8 106, of 21 at b = 4 74, of 6
+// for two columns at b = 8 33; others none or a few.  A spilled prefetch is waited
+// for where it is stored: in FP64 the first of these run at 4 to 5 us a level
+// instead of 0.6 to 1.2 (figures at use_pencil).
 constexpr int pencil_width(int bs, int max_width)
 {
     if (max_width <= 3) return 3;

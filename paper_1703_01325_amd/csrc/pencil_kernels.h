@@ -1,7 +1,7 @@
 // Pencil sweep for gfx950 (CDNA4, wave64): the level-scheduled sweep of one
 // unit-diagonal block triangular factor (Eq 4, Algorithm 7) on a pattern in
-// natural grid order, by blocks of grid lines.  Instantiated only in
-// pencil_b.hip (one translation unit per block size).
+// natural grid order, by blocks of grid lines.  Instantiated in pencil_b.hip
+// (one translation unit per block size) and, over a batch, in pencil_batch.hip.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -701,7 +701,8 @@ __global__ __launch_bounds__(256, (PencilRec<B, T, K>::waves(CB))) void k_sweep_
 // The same over a batch: tickets are (member, tile) pairs, each member with
 // arguments of its own in device memory.  One kernel holds every block size
 // at the width of ILU(0) on a grid (kPencilBatchWidth): their registers all
-// allow two workgroups per compute unit, which wider rows would halve.
+// allow two workgroups per compute unit, which wider rows would halve.  (The
+// largest blocks set the count: 38 registers spill in FP64, 29 in FP32.)
 // One application of 64 systems of 8 to 40 cells a side, blocks of 2 to 8
 // (1.3 GB of factors and vectors, 280 us at the rate of a copy): 1144 us with
 // a wavefront a row tile (k_sweep_batch), 467 us so.
