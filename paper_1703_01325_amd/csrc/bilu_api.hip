@@ -168,6 +168,9 @@ struct bilu_ctx {
     double* d_pw = nullptr;
     size_t pw_cap = 0;
     bool batch_member = false;  // applied by its batch, in the batch's work space
+    // layouts that a captured application reads (forward, transposed pair)
+    bool captured_pencil[2] = {false, false};
+    bool captured_tiles = false;
 
     double* d_y = nullptr;      // intermediate of an application, kept at kNotReady
     size_t y_cap = 0;
@@ -1004,6 +1007,21 @@ bool pencil_held(const bilu_ctx* c, int R)
     for (int w : {BILU_SWEEP_L, BILU_SWEEP_U})
         if (!c->h.pencil[w].built || c->pencil[w].vals_precision != c->precision) return false;
     return true;
+}
+
+// Remembers the layouts that an application of R columns reads if it is being
+// captured: a replay reads them after later factorisations, also where a knob of
+// the row tiles' launches has made applications take the other form since.
+void note_capture(bilu_ctx* c, bool pencil, bool transpose, int R, hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (status != hipStreamCaptureStatusActive) return;
+    if (pencil) c->captured_pencil[transpose ? 1 : 0] = true;
+    else if (sweep_form(c, R) == kFormTiled) c->captured_tiles = true;
 }
 
 // Work space of an application by pencil sweeps of R columns.
@@ -1905,6 +1923,10 @@ try {
     } else if ((st = layout_form(c, sweep_form(c, 1), s))) {
         return st;
     }
+    // what captured applications read
+    for (bool tr : {false, true})
+        if (c->captured_pencil[tr] && !row_tiles_asked(c) && (st = layout_pencil(c, tr, s))) return st;
+    if (c->captured_tiles && c->form_uploaded[kFormTiled] && (st = layout_form(c, kFormTiled, s))) return st;
     if (use_lines(c, BILU_SWEEP_L, 1) || use_lines(c, BILU_SWEEP_U, 1)) {
         if ((st = layout_form(c, kFormLines, s))) return st;
     }
@@ -1964,9 +1986,17 @@ bilu_status bilu_get_factors_f32(bilu_ctx* c, float* F, float* Dinv, hipStream_t
     return BILU_OK;
 }
 
+// do_apply for the caller's own programs, which may capture it.
+static bilu_status apply_entry(bilu_ctx* c, const double* r, double* z, int nrhs, bool transpose, hipStream_t s)
+{
+    const bilu_status st = do_apply(c, r, z, nrhs, transpose, s);
+    if (st == BILU_OK && c->h.bs <= kMaxKernelBs) note_capture(c, use_pencil(c, transpose, nrhs), transpose, nrhs, s);
+    return st;
+}
+
 bilu_status bilu_apply(bilu_ctx* c, const double* r, double* z, int nrhs, hipStream_t s)
 {
-    return do_apply(c, r, z, nrhs, false, s);
+    return apply_entry(c, r, z, nrhs, false, s);
 }
 
 bilu_status bilu_apply_noalloc(bilu_ctx* c, const double* r, double* z, int nrhs, hipStream_t s)
@@ -2022,6 +2052,7 @@ bilu_status bilu_apply_noalloc(bilu_ctx* c, const double* r, double* z, int nrhs
     // bilu_apply
     hipLaunchKernelGGL(dev::k_merge_status, dim3(1), dim3(64), 0, s, sync.status, c->d_status);
     CK(hipGetLastError());
+    note_capture(c, pencil, false, nrhs, s);
     return BILU_OK;
 }
 
@@ -2034,7 +2065,7 @@ bilu_status bilu_apply_point(bilu_ctx* c, const double* r, double* z, hipStream_
 
 bilu_status bilu_apply_transpose(bilu_ctx* c, const double* r, double* z, int nrhs, hipStream_t s)
 {
-    return do_apply(c, r, z, nrhs, true, s);
+    return apply_entry(c, r, z, nrhs, true, s);
 }
 
 bilu_status bilu_spmv(bilu_ctx* c, const double* Ax, const double* x, double* y, int nrhs, int transpose,

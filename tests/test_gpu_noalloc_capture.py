@@ -123,3 +123,44 @@ def test_noalloc_after_another_layout_is_asked_for(api):
         assert torch.equal(z, want)
         M.check()
         M.close()
+
+
+@pytest.mark.parametrize("call", ["noalloc", "apply", "transpose"])
+@pytest.mark.parametrize("before,after", [({}, dict(helper=True)), (dict(split_dinv=False), dict(split_dinv="auto"))],
+                         ids=["pencils", "tiles"])
+def test_replay_after_a_launch_knob_and_a_factorisation(api, call, before, after):
+    """A captured application reads the factors of the last factorisation, also
+    where a launch knob has made later ones take the other form."""
+    s = synth.reservoir(11, 9, 10, 3, seed=25)
+    Ax = torch.from_numpy(s.Ax).cuda()
+    M = api.BlockILU(s.nb, s.bs, s.Ap, s.Aj, 0, transpose=True)
+    P = api.BlockILU(s.nb, s.bs, s.Ap, s.Aj, 0, transpose=True)
+    M.tune(**before)
+    assert M.factor(Ax) == -1
+    r = torch.randn(s.n, dtype=torch.float64, device="cuda")
+    z = torch.empty_like(r)
+
+    def run(B, out):
+        if call == "noalloc":
+            _noalloc(B, r, out)
+        else:
+            B.apply(r, out=out, transpose=call == "transpose")
+
+    run(M, z)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        run(M, z)
+    M.tune(**after)
+    for scale in (2.0, 0.5, 3.0):
+        values = scale * Ax
+        assert M.factor(values) == -1 and P.factor(values) == -1
+        want = torch.empty_like(r)
+        run(P, want)
+        for _ in range(2):
+            z.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(z, want)
+            assert torch.equal(M.apply(r, transpose=call == "transpose"), want)
+    M.check()
