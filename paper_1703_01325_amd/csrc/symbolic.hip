@@ -47,10 +47,10 @@ namespace {
 
 constexpr int kHash = 1024;          // hash slots of the largest row search; it may reach 3/4 as many vertices
 // Up to this many rows a search is its launches and allocations: one launch with
-// the largest table (7 points, one launch against small tables and lists: k = 1,
-// 8000 rows 306 and 355 us, 15625 rows 372 and 332; k = 0, 15625 rows 293 and 311,
-// 27000 rows 341 and 310).
-constexpr int few_rows(int k) { return k == 0 ? 24000 : 10000; }
+// the largest table (7 points, one launch against small tables and lists: 15625
+// rows k = 0 293 and 311 us; 8000 rows k = 1 306 and 355, k = 3 427 and 388; 4096
+// rows k = 2 292 and 332, k = 4 371 and 320).
+constexpr int few_rows(int k) { return 24000 / (2 * k + 1); }
 constexpr unsigned short kKept = 0x8000u;
 constexpr unsigned int kSpinLimit = 1u << 20;
 
@@ -84,8 +84,10 @@ __global__ void k_check_pattern(int nb, const int32_t* __restrict__ Ap, const in
     }
 }
 
+// (and the entry count, status[1])
 __global__ void k_check_ptr(int nb, const int32_t* __restrict__ Ap, int* status)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) status[1] = Ap[nb];
     if (blockIdx.x == 0 && threadIdx.x == 0 && Ap[0] != 0) atomicOr(status, kStPattern);
 }
 
@@ -108,16 +110,16 @@ template <int SLOTS>
 __device__ __forceinline__ int table_slot(RowTable<SLOTS>& t, int v)
 {
     unsigned int h = (static_cast<unsigned int>(v) * 2654435761u) >> (32 - slot_bits(SLOTS));
-    for (int probe = 0; probe < SLOTS; ++probe) {
+    // (so far, so that a table that is given up when it is nearly full costs the
+    // vertices in flight no more; the largest table is probed to the end)
+    constexpr int kProbes = SLOTS < kHash && SLOTS > 64 ? 64 : SLOTS;
+    for (int probe = 0; probe < kProbes; ++probe) {
         const int old = atomicCAS(&t.key[h], -1, v);
         if (old == v) return static_cast<int>(h);
         if (old == -1) {
             if (atomicAdd(&t.nused, 1) >= SLOTS / 4 * 3) t.over = 1;
             return static_cast<int>(h);
         }
-        // (a table given up is not filled to its last slot: every vertex more
-        // would probe all of it)
-        if (__hip_atomic_load(&t.over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) return -1;
         h = (h + 1) & (SLOTS - 1);
     }
     t.over = 1;
@@ -168,7 +170,11 @@ __global__ __launch_bounds__(64) void k_sym_rows(int nb, const int32_t* __restri
         }
         __syncthreads();
         // row i of A: level 0, no inner vertex (M = -1)
-        if (live) {
+        // (a table given up is not searched on: every vertex more would probe all
+        // of a full one)
+        if (live && Ap[i + 1] - Ap[i] > SLOTS / 4 * 3) {
+            if (lane == 0) t.over = 1;
+        } else if (live) {
             for (int e = Ap[i] + lane; e < Ap[i + 1]; e += LANES) {
                 const int v = Aj[e];
                 const int s = table_slot(t, v);
@@ -185,6 +191,7 @@ __global__ __launch_bounds__(64) void k_sym_rows(int nb, const int32_t* __restri
             if (!__any(nf)) break;
             // extend the paths ending in the frontier by one edge of A
             for (int f = lane / kEdges; f < nf; f += LANES / kEdges) {
+                if (__hip_atomic_load(&t.over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
                 const int su = t.list[f];
                 const int u = t.key[su];
                 const int mu = max(t.mval[su], u);
@@ -566,7 +573,7 @@ bilu_status sym_count(int nb, const int32_t* Ap, const int32_t* Aj, int k, int32
                       hipStream_t s)
 {
     Scratch sc;
-    int* d_status = sc.get<int>(1);
+    int* d_status = sc.get<int>(2);
     int32_t* cnt = sc.get<int32_t>(static_cast<size_t>(nb) + 1);
     int64_t* ptr64 = sc.get<int64_t>(static_cast<size_t>(nb) + 1);
     if (!d_status || !cnt || !ptr64) return BILU_ERR_ALLOC;
@@ -574,12 +581,11 @@ bilu_status sym_count(int nb, const int32_t* Ap, const int32_t* Aj, int k, int32
     CKH(hipMemsetAsync(cnt + nb, 0, sizeof(int32_t), s));
     k_check_ptr<<<1, 64, 0, s>>>(nb, Ap, d_status);
     k_check_pattern<<<grid_for(nb, 256), 256, 0, s>>>(nb, Ap, Aj, d_status);
-    int h_status = 0;
-    *nnzA = 0;
-    CKH(hipMemcpyAsync(&h_status, d_status, sizeof(int), hipMemcpyDeviceToHost, s));
-    if (nb > few_rows(k)) CKH(hipMemcpyAsync(nnzA, Ap + nb, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    int h_small[2] = {0, 0}, h_status = 0;
+    CKH(hipMemcpyAsync(h_small, d_status, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     CKH(hipStreamSynchronize(s));
-    if (h_status) return status_to_error(h_status);
+    if (h_small[0]) return status_to_error(h_small[0]);
+    *nnzA = h_small[1];
     const bilu_status st = search_rows<false>(nb, *nnzA, Ap, Aj, k, cnt, nullptr, nullptr, nullptr, d_status, sc, s);
     if (st != BILU_OK) return st;
     size_t tmp_bytes = 0;
