@@ -123,7 +123,7 @@ def run_gpu(args, sysm, k, precision, R=1, steps=None, warmup=None, method="bicg
     pair_us = sum(per[kk]["avg_us"] for kk in ("sweep_L", "sweep_U", "spmv") if kk in per)
     pair_bytes = ab["sweep_L"] + ab["sweep_U"] + ab["spmv"]
     return {
-        "M": M, "info": info, "analyze_s": analyze_s, "elapsed": elapsed, "steps": steps,
+        "M": M, "info": info, "form": M.sweep_info(R)["form"][0], "analyze_s": analyze_s, "elapsed": elapsed, "steps": steps,
         "status": int(st), "iters": [int(i[1]) for i in inf], "relres": [float(i[2]) for i in inf],
         "x_err": err, "per_kernel": per, "bytes": ab,
         "pair_us": pair_us, "pair_GBps": pair_bytes / pair_us / 1e3,
@@ -138,7 +138,7 @@ def variant_line(res, R=1):
             "solves_per_s": R * res["steps"] / res["elapsed"],
             "status": res["status"], "iters": max(res["iters"]), "relres": max(res["relres"]),
             "pair_us": res["pair_us"], "apply_spmv_GBps": res["pair_GBps"],
-            "frac_of_hbm_peak": res["pair_GBps"] / HBM_PEAK_GBPS,
+            "frac_of_hbm_peak": res["pair_GBps"] / HBM_PEAK_GBPS, "sweep_form": res["form"],
             "kernels_us": {kk: round(v["avg_us"], 2) for kk, v in res["per_kernel"].items()},
             "roofline": {kk: rf[kk] for kk in ("kernel", "achieved", "frac", "avg_launch_us") if kk in rf}}
 
@@ -194,7 +194,7 @@ def run_poisson_table(args, n=120, sizes=(1, 2, 4, 8), levels=(0, 1, 2, 3), rtol
                    "factor_ms": factor_ms, "ms_per_iter": round(v["ms_per_solve"] / max(v["iters"], 1), 4),
                    "levels_L": int(info.nlev[0]), "nnzb_L": int(info.nnzb_L),
                    "pair_us": round(v["pair_us"], 2), "apply_spmv_GBps": round(v["apply_spmv_GBps"], 1),
-                   "kernels_us": v["kernels_us"], "roofline": v["roofline"]}
+                   "sweep_form": v["sweep_form"], "kernels_us": v["kernels_us"], "roofline": v["roofline"]}
             if (bs, k) in PAPER_TABLE1:
                 row["paper_k20xm"] = {"gpu_s": PAPER_TABLE1[(bs, k)][0], "iters": PAPER_TABLE1[(bs, k)][1]}
             rows.append(row)
@@ -481,7 +481,7 @@ def main():
         "x_rel_err_vs_xstar": res["x_err"],
         "analyze_s": res["analyze_s"],
         "apply_spmv": {"pair_us": res["pair_us"], "GBps": res["pair_GBps"],
-                       "frac_of_hbm_peak": res["pair_GBps"] / HBM_PEAK_GBPS},
+                       "frac_of_hbm_peak": res["pair_GBps"] / HBM_PEAK_GBPS, "sweep_form": res["form"]},
         "kernels": {kk: {"avg_us": round(v["avg_us"], 2), "launches": v["launches"]}
                     for kk, v in res["per_kernel"].items()},
         "roofline": roofline_of(res),

@@ -110,8 +110,8 @@ template <int SLOTS>
 __device__ __forceinline__ int table_slot(RowTable<SLOTS>& t, int v)
 {
     unsigned int h = (static_cast<unsigned int>(v) * 2654435761u) >> (32 - slot_bits(SLOTS));
-    // (so far, so that a table that is given up when it is nearly full costs the
-    // vertices in flight no more; the largest table is probed to the end)
+    // (no further than this, so that the vertices in flight when a table is given up
+    // do not probe all of a full one; the largest is probed to its end)
     constexpr int kProbes = SLOTS < kHash && SLOTS > 64 ? 64 : SLOTS;
     for (int probe = 0; probe < kProbes; ++probe) {
         const int old = atomicCAS(&t.key[h], -1, v);
