@@ -164,3 +164,28 @@ def test_replay_after_a_launch_knob_and_a_factorisation(api, call, before, after
             assert torch.equal(z, want)
             assert torch.equal(M.apply(r, transpose=call == "transpose"), want)
     M.check()
+
+
+@pytest.mark.parametrize("grid,b,k,R", [((60, 220, 85), 3, 0, 1), ((31, 33, 42), 3, 1, 32), ((19, 21, 40), 8, 0, 32),
+                                        ((70, 70, 70), 1, 0, 12)],
+                         ids=["1col", "32cols", "b8", "b1"])
+def test_noalloc_near_the_scratch_limit(api, grid, b, k, R):
+    """Vectors and exchange arrays of close to the most columns the call takes."""
+    Ap, Aj = synth.stencil7_pattern(*grid)
+    nb = Ap.size - 1
+    assert 0.75 * 2 ** 25 < 8 * nb * b * R <= 2 ** 25 - 256
+    gen = torch.Generator(device="cuda").manual_seed(R)
+    rows = torch.repeat_interleave(torch.arange(nb), torch.from_numpy(Ap).diff())
+    Ax = 0.1 * torch.randn(Aj.size, b, b, generator=gen, dtype=torch.float64, device="cuda")
+    Ax[(torch.from_numpy(Aj) == rows).cuda()] += (2.0 + b) * torch.eye(b, dtype=torch.float64, device="cuda")
+    M = api.BlockILU(nb, b, Ap, Aj, k)
+    assert M.factor(Ax.reshape(-1)) == -1
+    assert M.sweep_info(R)["form"] == ("pencils", "pencils")
+    r = torch.randn((nb * b,) if R == 1 else (nb * b, R), generator=gen, dtype=torch.float64, device="cuda")
+    z = torch.empty_like(r)
+    for _ in range(2):
+        z.zero_()
+        _noalloc(M, r, z)
+        assert torch.equal(z, M.apply(r))
+    M.check()
+    M.close()
